@@ -13,7 +13,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmithra.so")
-SOURCES = ["engine.hip", "k_fdtd.hip", "k_particles.hip", "k_sort.hip"]
+SOURCES = ["engine.hip", "k_fdtd.hip", "k_particles.hip", "k_sort.hip", "k_read.hip"]
 
 HIPCC_FLAGS = [
     "-I" + os.path.join(os.path.dirname(HERE), "include"),
@@ -46,7 +46,7 @@ def build_library(verbose: bool = False) -> str:
             raise RuntimeError(f"hipcc failed on {src}:\n{r.stderr}")
         return obj
 
-    with ThreadPoolExecutor(max_workers=min(4, len(SOURCES))) as ex:
+    with ThreadPoolExecutor(max_workers=min(5, len(SOURCES))) as ex:
         objs = list(ex.map(compile_one, SOURCES))
     tmp = LIB + ".tmp"
     cmd = [hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs]

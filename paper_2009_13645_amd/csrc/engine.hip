@@ -42,6 +42,10 @@ hipError_t launch_gen_bunch(const RunDev &R, const GenParams &P, int pass, doubl
 hipError_t launch_push_deposit(const RunDev &R, hipStream_t st, bool box, bool end_step);
 hipError_t launch_load_deposit(const RunDev &R, hipStream_t st);
 hipError_t launch_bunching(const RunDev &R, double *part, int blocks, hipStream_t st);
+hipError_t launch_read_convert(const RunDev &R, const void *a, const void *lo, void *out, bool out64, hipStream_t st);
+hipError_t launch_read_vertex(const RunDev &R, int64_t s, int id, void *out, bool out64, hipStream_t st);
+hipError_t launch_read_particles(const RunDev &R, double *xyz, double *u, int32_t *cell, int32_t *order,
+                                 hipStream_t st);
 hipError_t launch_sort(const RunDev &R, hipStream_t st, bool keys_ready, int step_tail = 0);
 // launch_sort with step_tail runs the box reductions before the sort and
 // ends the step after it, in one workgroup, when this holds
@@ -559,26 +563,6 @@ static int finish_load(mithra_handle h, int64_t n, double q_macro)
     return MITHRA_OK;
 }
 
-// cell index per id, written beside the sort keys (read back on request)
-__global__ void k_cells_by_id(RunDev R, int32_t *cell_by_id)
-{
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= R.np)
-        return;
-    const int pb = R.ctl->pbuf;
-    const double g[3] = {(R.pr[pb][0][p] - R.x0) / R.dx, (R.pr[pb][1][p] - R.y0) / R.dy,
-                         (R.pr[pb][2][p] - R.z0) / R.dz};
-    const int n[3] = {R.nx, R.ny, R.nz};
-    int c[3];
-    bool act = true;
-    for (int a = 0; a < 3; ++a) {
-        const double f = floor(g[a]);
-        act = act && f >= 1.0 && f <= (double)(n[a] - 3);
-        c[a] = act ? (int)f : 0;
-    }
-    cell_by_id[R.pid[pb][p]] = act ? (int32_t)nid(R, c[0], c[1], c[2]) : -1;
-}
-
 static int enqueue_sort_with_cells(mithra_handle h)
 {
     HIPCHK(h, launch_sort(h->R, h->stream, false));
@@ -759,25 +743,18 @@ extern "C" int mithra_read_fields(mithra_handle h, int field_id, int dtype, void
     const size_t pf = R.precision == 32 ? 4 : 8;
     const int64_t S = h->steps;
     const char *src = nullptr, *lo = nullptr;
+    // device scratch of a read: the time level that the next step's sweep
+    // writes (slot_next; only the A components, phi's are zero for good in a
+    // run without space charge).  12 bytes a node and more: it holds the
+    // result as FP64 too.
+    char *tmp = (char *)R.pot + (size_t)slot_next(S) * 4 * nn * pf;
     if (field_id <= MITHRA_FIELD_BZ) {
         if (S == 0) {
             memset(host_out, 0, bytes);
             return MITHRA_OK;
         }
-        HIPCHK(h, launch_vertex_fields(R, -1, 1, h->stream));
-        HIPCHK(h, sync_run(h));
-        // node-interleaved: 8 words per node, component field_id
-        std::vector<char> all(8 * nn * pf);
-        HIPCHK(h, hipMemcpy(all.data(), R.eb, all.size(), hipMemcpyDeviceToHost));
-        for (size_t i = 0; i < nn; ++i) {
-            const double v = pf == 4 ? (double)((const float *)all.data())[8 * i + field_id]
-                                     : ((const double *)all.data())[8 * i + field_id];
-            if (esz == 4)
-                ((float *)host_out)[i] = (float)v;
-            else
-                ((double *)host_out)[i] = v;
-        }
-        return MITHRA_OK;
+        HIPCHK(h, launch_read_vertex(R, S - 1, field_id, tmp, esz == 8, h->stream));
+        src = tmp;
     } else if (field_id <= MITHRA_FIELD_AZ || field_id == MITHRA_FIELD_PHI) {
         const int comp = field_id == MITHRA_FIELD_PHI ? 3 : field_id - MITHRA_FIELD_AX;
         src = (const char *)R.pot + ((size_t)slot_cur(S) * 4 + comp) * nn * pf;
@@ -788,21 +765,12 @@ extern "C" int mithra_read_fields(mithra_handle h, int field_id, int dtype, void
         if (R.src_lo)
             lo = (const char *)R.src_lo + o;
     }
-    std::vector<char> raw(nn * pf), rawlo;
-    HIPCHK(h, hipMemcpy(raw.data(), src, nn * pf, hipMemcpyDeviceToHost));
-    if (lo) {
-        rawlo.resize(nn * pf);
-        HIPCHK(h, hipMemcpy(rawlo.data(), lo, nn * pf, hipMemcpyDeviceToHost));
+    if (src != tmp && (lo || esz != pf)) {
+        HIPCHK(h, launch_read_convert(R, src, lo, tmp, esz == 8, h->stream));
+        src = tmp;
     }
-    for (size_t i = 0; i < nn; ++i) {
-        double v = pf == 4 ? (double)((const float *)raw.data())[i] : ((const double *)raw.data())[i];
-        if (lo)
-            v += (double)((const float *)rawlo.data())[i];
-        if (esz == 4)
-            ((float *)host_out)[i] = (float)v;
-        else
-            ((double *)host_out)[i] = v;
-    }
+    HIPCHK(h, hipMemcpyAsync(host_out, src, bytes, hipMemcpyDeviceToHost, h->stream));
+    HIPCHK(h, hipStreamSynchronize(h->stream));
     return MITHRA_OK;
 }
 
@@ -817,42 +785,24 @@ extern "C" int mithra_read_particles(mithra_handle h, double *xyz, double *u, in
     if (rc)
         return rc;
     RunDev &R = h->R;
-    const int64_t n = R.np;
-    int32_t pb = 0;
-    HIPCHK(h, hipMemcpy(&pb, &R.ctl->pbuf, 4, hipMemcpyDeviceToHost));
-    // the state sits in buffer pb in the slots pid[pb]; the order of the
-    // last sort is the slot list sv[sorted_buf] (the push does not move the
-    // state after sorting)
-    std::vector<int32_t> ids((size_t)n);
-    HIPCHK(h, hipMemcpy(ids.data(), R.pid[pb], (size_t)n * 4, hipMemcpyDeviceToHost));
-    if (sort_perm) {
-        int32_t sb = 0;
-        HIPCHK(h, hipMemcpy(&sb, &R.ctl->sorted_buf, 4, hipMemcpyDeviceToHost));
-        std::vector<int32_t> slots((size_t)n);
-        if (sb < 0)  // no sort after the last push: the buffer order
-            for (int64_t r = 0; r < n; ++r)
-                slots[(size_t)r] = (int32_t)r;
-        else
-            HIPCHK(h, hipMemcpy(slots.data(), R.sv[sb], (size_t)n * 4, hipMemcpyDeviceToHost));
-        for (int64_t r = 0; r < n; ++r)
-            sort_perm[r] = ids[(size_t)slots[(size_t)r]];
-    }
-    std::vector<double> col((size_t)n);
-    for (int a = 0; a < 6; ++a) {
-        double *dst = a < 3 ? xyz : u;
-        if (!dst)
-            continue;
-        HIPCHK(h, hipMemcpy(col.data(), R.pr[pb][a], (size_t)n * 8, hipMemcpyDeviceToHost));
-        for (int64_t r = 0; r < n; ++r)
-            dst[3 * (int64_t)ids[(size_t)r] + (a % 3)] = col[(size_t)r];
-    }
-    if (cell) {
-        hipLaunchKernelGGL(k_cells_by_id, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, h->stream, R,
-                           h->cell_by_id);
-        HIPCHK(h, hipGetLastError());
-        HIPCHK(h, sync_run(h));
-        HIPCHK(h, hipMemcpy(cell, h->cell_by_id, (size_t)n * 4, hipMemcpyDeviceToHost));
-    }
+    const size_t n = (size_t)R.np;
+    // device scratch of a read: the particle buffer that the next push
+    // writes (six contiguous columns, the other one than pbuf, which flips
+    // with every step), and the sort's input arrays, rewritten by the push
+    // before each sort
+    double *rows = R.pr[(h->steps + 1) & 1][0];
+    int32_t *cells = h->cell_by_id, *order = R.slot_in;
+    HIPCHK(h, launch_read_particles(R, xyz ? rows : nullptr, u ? rows + 3 * n : nullptr, cell ? cells : nullptr,
+                                    sort_perm ? order : nullptr, h->stream));
+    if (xyz)
+        HIPCHK(h, hipMemcpyAsync(xyz, rows, 3 * n * 8, hipMemcpyDeviceToHost, h->stream));
+    if (u)
+        HIPCHK(h, hipMemcpyAsync(u, rows + 3 * n, 3 * n * 8, hipMemcpyDeviceToHost, h->stream));
+    if (cell)
+        HIPCHK(h, hipMemcpyAsync(cell, cells, n * 4, hipMemcpyDeviceToHost, h->stream));
+    if (sort_perm)
+        HIPCHK(h, hipMemcpyAsync(sort_perm, order, n * 4, hipMemcpyDeviceToHost, h->stream));
+    HIPCHK(h, hipStreamSynchronize(h->stream));
     return MITHRA_OK;
 }
 
