@@ -29,7 +29,8 @@
 namespace mithra {
 hipError_t launch_sweep(const RunDev &R, int shape, hipStream_t st);
 int sweep_shape_count();
-void sweep_shape_dims(int shape, int *tx, int *ty, int *tz);
+int sweep_default_shape(int nx, int ny, int nz, int precision);
+int sweep_effective_shape(const RunDev &R, int shape);
 hipError_t launch_mur(const RunDev &R, hipStream_t st);
 hipError_t launch_mur_faces(const RunDev &R, hipStream_t st);
 int sweep_fuses_xfaces(const RunDev &R, int shape);
@@ -488,17 +489,7 @@ extern "C" int mithra_init_grid(const mithra_grid_desc *d, void *dev_arena, size
         box_slot_empty(&slots[16 * b]);
     HIPCHK(h, hipMemcpyAsync(R.boxslot, slots.data(), slots.size() * 4, hipMemcpyHostToDevice, h->stream));
     HIPCHK(h, sync_run(h));
-    // default sweep tile (measured): grids of up to 2^20 nodes take chunks
-    // of 4 or 16 planes, so that enough workgroups run (vector tiles when the
-    // row length allows 16-byte vectors, else the scalar tiles); larger grids
-    // take vector tiles 32 nodes wide for short rows, else 64 nodes wide over
-    // 16 planes (the best at 128-node rows)
-    const int vec = d->field_precision == 32 ? 4 : 2;
-    const bool small = (double)d->nx * d->ny * d->nz <= 1048576.0;
-    if (d->nx % vec == 0)
-        h->sweep_shape = small ? 15 : (d->nx <= 48 ? 13 : 17);
-    else
-        h->sweep_shape = small ? 6 : ((d->nx - 2 <= 40) ? 2 : 0);
+    h->sweep_shape = sweep_default_shape(d->nx, d->ny, d->nz, d->field_precision);
     const char *sh = getenv("MITHRA_SWEEP_SHAPE");
     if (sh)
         h->sweep_shape = atoi(sh) % sweep_shape_count();
@@ -1314,7 +1305,7 @@ extern "C" int mithra_autotune_sweep(mithra_handle h, int iters, int *best_shape
     float best_t = 1e30f;
     for (int sh = 0; sh < sweep_shape_count(); ++sh) {
         if (sh >= 8 && h->R.nx % V != 0)
-            continue;  // falls back to shape 0, timed already
+            continue;  // runs a scalar tile, timed already
         RunDev R = h->R;
         R.xface_fused = sweep_fuses_xfaces(R, sh);
         HIPCHK(h, launch_sweep(R, sh, h->stream));
@@ -1468,12 +1459,6 @@ static int make_tab(mithra_batch b, const std::vector<int> &mem, NB nb, GroupTab
     return MITHRA_OK;
 }
 
-static int effective_shape(const mithra_handle h)
-{
-    const int V = h->R.precision == 32 ? 4 : 2;
-    return (h->sweep_shape >= 8 && h->R.nx % V != 0) ? 0 : h->sweep_shape;
-}
-
 static int build_tables(mithra_batch b)
 {
     const int n = (int)b->runs.size();
@@ -1484,7 +1469,7 @@ static int build_tables(mithra_batch b)
     std::map<std::tuple<int, int, int>, std::vector<int>> cls;
     for (int i = 0; i < n; ++i) {
         const mithra_handle h = b->runs[i];
-        cls[{h->R.precision, h->R.compensated, effective_shape(h)}].push_back(i);
+        cls[{h->R.precision, h->R.compensated, sweep_effective_shape(h->R, h->sweep_shape)}].push_back(i);
     }
     for (auto &kv : cls) {
         mithra_batch_s::SweepCls c{std::get<0>(kv.first), std::get<1>(kv.first), std::get<2>(kv.first), {}};
@@ -1723,7 +1708,7 @@ extern "C" int mithra_batch_autotune_sweep(mithra_batch b, int iters, int32_t *s
         float best_t = 1e30f;
         for (int sh = 0; sh < sweep_shape_count() && !rc; ++sh) {
             if (sh >= 8 && !any_vec)
-                continue;  // every member would fall back to shape 0
+                continue;  // every member would run its default scalar tile
             for (int i : kv.second)
                 member_set_shape(b->runs[i], sh);
             rc = rebuild_tables(b);

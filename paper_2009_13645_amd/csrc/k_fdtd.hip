@@ -1081,10 +1081,6 @@ struct SeedInject {
 // host launchers
 // ---------------------------------------------------------------------------
 
-struct SweepShape {
-    int tx, ty, tz;
-};
-
 template <typename T, int TX, int TY, int TZ>
 static hipError_t launch_sweep_t(const RunDev &R, hipStream_t st)
 {
@@ -1112,54 +1108,100 @@ static hipError_t launch_sweep_vec_t(const RunDev &R, hipStream_t st)
     return hipGetLastError();
 }
 
-int sweep_fuses_xfaces(const RunDev &R, int shape)
+// Tiles of the sweep: x nodes, y rows (FP32; the vector tiles' rows halve at
+// FP64), z planes.  0..7 scalar (one node per thread), 8..17 vector (16
+// bytes per thread).  Workgroups of 256 threads, 5 and 12 of 512: other
+// tiles of 512 threads were slower on grids that leave CUs idle and no
+// faster on large ones (in the step of the 128 x 128 x 1024 run: 64 x 32 x
+// 16 nodes in 512 threads 166 us at FP32 and 309 at FP64, 64 x 16 x 16 in
+// 256 162 and 302; tiles over 32 or 64 planes 169 and more).
+static const int kSweepTile[18][3] = {{64, 4, 16}, {64, 4, 4},  {32, 8, 4},  {64, 4, 8},   {32, 8, 8},   {64, 8, 32},
+                                      {32, 8, 16}, {16, 16, 4}, {16, 64, 4}, {32, 32, 4},  {32, 32, 8},  {32, 32, 16},
+                                      {128, 16, 8}, {64, 16, 4}, {64, 16, 8}, {64, 16, 16}, {128, 8, 4}, {128, 8, 16}};
+
+int sweep_shape_count() { return 18; }
+
+// Vector tiles need rows that start on 16 bytes.
+static bool sweep_aligned(int nx, int precision) { return nx % (precision == 32 ? 4 : 2) == 0; }
+
+static int64_t sweep_tiles(int nx, int ny, int nz, int precision, int shape)
 {
-    const int V = R.precision == 32 ? 4 : 2;
-    return (shape >= 8 && R.nx % V == 0) ? 1 : 0;
+    const int *d = kSweepTile[shape];
+    const int ty = shape >= 8 && precision == 64 ? d[1] / 2 : d[1];
+    return (int64_t)((nx + d[0] - 1) / d[0]) * ((ny + ty - 1) / ty) * ((nz - 2 + d[2] - 1) / d[2]) * 4;
 }
+
+// Default tile of a grid: the least estimated time, in units of one plane of
+// a workgroup (about 0.4 us), from what bounds a sweep:
+//  * the planes that the workgroups run one after the other: rounds of
+//    resident workgroups (at least one) times the planes of a tile and its
+//    prologue.  Few planes fill the device on a small grid;
+//  * the bytes of a node: three streams, and psi^n again for each tile's
+//    two extra planes, its halo rows and the partly used vectors at its
+//    row ends.  Many planes and wide tiles read less on a large grid.
+// The constants were fitted on 70 aligned and 40 unaligned grids (12..129 x
+// 12..128 x 40..2800, both precisions, every tile timed): the choice is
+// within 3 % of the best tile in the mean and 25 % at worst; the earlier rule
+// (two tiles by the node count, a third for short rows) was 35 % off in the
+// mean.  Sweep alone, before and after: 64 x 64 x 256 FP64 37.4 -> 21.5 us,
+// 96 x 80 x 192 FP32 31.3 -> 21.4, 24 x 24 x 400 FP32 19.5 -> 8.8, 45 x 51 x
+// 97 FP32 19.9 -> 9.0; in the step of the 128 x 128 x 1024 run FP32 166 -> 162,
+// FP64 309 -> 302.
+int sweep_default_shape(int nx, int ny, int nz, int precision)
+{
+    const bool vec = sweep_aligned(nx, precision);
+    const double slots = vec ? 576 : 1500, prologue = vec ? 1.5 : 0.5, row_end = vec ? 24 : 8;
+    const double mb = 4e-6 * nx * ny * nz * (precision / 8);
+    int best = -1;
+    double best_cost = 0;
+    for (int s = vec ? 8 : 0; s < (vec ? 18 : 8); ++s) {
+        const int *d = kSweepTile[s];
+        const double ty = vec && precision == 64 ? d[1] / 2 : d[1], tz = d[2];
+        const double n = (double)sweep_tiles(nx, ny, nz, precision, s) * (s == 5 || s == 12 ? 2 : 1);
+        const double cost = std::max(1.0, n / slots) * (tz + prologue) +
+                            mb * (3 + 2 / tz + 5 / ty * (1 + 2 / tz) + row_end / d[0]) / 13;
+        if (best < 0 || cost < best_cost) {
+            best = s;
+            best_cost = cost;
+        }
+    }
+    return best;
+}
+
+// The tile that runs for a chosen one: a vector tile on unaligned rows is
+// replaced by the grid's default (scalar) tile.
+int sweep_effective_shape(const RunDev &R, int shape)
+{
+    return shape >= 8 && !sweep_aligned(R.nx, R.precision) ? sweep_default_shape(R.nx, R.ny, R.nz, R.precision) : shape;
+}
+
+int sweep_fuses_xfaces(const RunDev &R, int shape) { return shape >= 8 && sweep_aligned(R.nx, R.precision) ? 1 : 0; }
 
 template <typename T>
 static hipError_t launch_sweep_shape(const RunDev &R, int shape, hipStream_t st)
 {
     constexpr int V = 16 / sizeof(T);
-    if (shape >= 8 && R.nx % V != 0)
-        shape = 0;  // vector tiles need aligned rows
-    switch (shape) {
-    case 8: return launch_sweep_vec_t<T, V, 128 / V, 512 * V / 128, 32>(R, st);
-    case 9: return launch_sweep_vec_t<T, V, 128 / V, 256 * V / 128, 32>(R, st);
-    case 10: return launch_sweep_vec_t<T, V, 64 / V, 512 * V / 64, 32>(R, st);
-    case 11: return launch_sweep_vec_t<T, V, 128 / V, 512 * V / 128, 16>(R, st);
-    case 12: return launch_sweep_vec_t<T, V, 128 / V, 512 * V / 128, 64>(R, st);
-    case 13: return launch_sweep_vec_t<T, V, 32 / V, 256 * V / 32, 32>(R, st);
-    case 14: return launch_sweep_vec_t<T, V, 128 / V, 256 * V / 128, 16>(R, st);
-    case 15: return launch_sweep_vec_t<T, V, 128 / V, 512 * V / 128, 4>(R, st);
-    case 16: return launch_sweep_vec_t<T, V, 128 / V, 1024 * V / 128, 16>(R, st);
-    case 17: return launch_sweep_vec_t<T, V, 64 / V, 512 * V / 64, 16>(R, st);
-    case 0: return launch_sweep_t<T, 64, 8, 32>(R, st);
-    case 1: return launch_sweep_t<T, 64, 4, 32>(R, st);
-    case 2: return launch_sweep_t<T, 32, 8, 32>(R, st);
-    case 3: return launch_sweep_t<T, 64, 8, 64>(R, st);
-    case 4: return launch_sweep_t<T, 128, 4, 32>(R, st);
-    case 5: return launch_sweep_t<T, 64, 16, 32>(R, st);
-    case 6: return launch_sweep_t<T, 32, 4, 16>(R, st);
-    case 7: return launch_sweep_t<T, 64, 8, 16>(R, st);
+    switch (sweep_effective_shape(R, shape)) {
+    case 8: return launch_sweep_vec_t<T, V, 16 / V, 256 * V / 16, 4>(R, st);
+    case 9: return launch_sweep_vec_t<T, V, 32 / V, 256 * V / 32, 4>(R, st);
+    case 10: return launch_sweep_vec_t<T, V, 32 / V, 256 * V / 32, 8>(R, st);
+    case 11: return launch_sweep_vec_t<T, V, 32 / V, 256 * V / 32, 16>(R, st);
+    case 12: return launch_sweep_vec_t<T, V, 128 / V, 512 * V / 128, 8>(R, st);
+    case 13: return launch_sweep_vec_t<T, V, 64 / V, 256 * V / 64, 4>(R, st);
+    case 14: return launch_sweep_vec_t<T, V, 64 / V, 256 * V / 64, 8>(R, st);
+    case 15: return launch_sweep_vec_t<T, V, 64 / V, 256 * V / 64, 16>(R, st);
+    case 16: return launch_sweep_vec_t<T, V, 128 / V, 256 * V / 128, 4>(R, st);
+    case 17: return launch_sweep_vec_t<T, V, 128 / V, 256 * V / 128, 16>(R, st);
+    case 0: return launch_sweep_t<T, 64, 4, 16>(R, st);
+    case 1: return launch_sweep_t<T, 64, 4, 4>(R, st);
+    case 2: return launch_sweep_t<T, 32, 8, 4>(R, st);
+    case 3: return launch_sweep_t<T, 64, 4, 8>(R, st);
+    case 4: return launch_sweep_t<T, 32, 8, 8>(R, st);
+    case 5: return launch_sweep_t<T, 64, 8, 32>(R, st);
+    case 6: return launch_sweep_t<T, 32, 8, 16>(R, st);
+    case 7: return launch_sweep_t<T, 16, 16, 4>(R, st);
     default: return hipErrorInvalidValue;
     }
-}
-
-int sweep_shape_count() { return 18; }
-
-// Tile of each shape in nodes (x, y, z) for FP32; shapes 8..13 are the
-// vector kernels (4 FP32 or 2 FP64 nodes per thread; y rows halve in FP64).
-void sweep_shape_dims(int shape, int *tx, int *ty, int *tz)
-{
-    static const int d[18][3] = {{64, 8, 32},  {64, 4, 32},  {32, 8, 32},  {64, 8, 64},  {128, 4, 32},
-                                 {64, 16, 32}, {32, 4, 16},  {64, 8, 16},  {128, 16, 32}, {128, 8, 32},
-                                 {64, 32, 32}, {128, 16, 16}, {128, 16, 64}, {32, 32, 32}, {128, 8, 16},
-                                 {128, 16, 4}, {128, 32, 16}, {64, 32, 16}};
-    *tx = d[shape][0];
-    *ty = d[shape][1];
-    *tz = d[shape][2];
 }
 
 // boundary nodes the Mur kernel updates (see Mur)
@@ -1285,16 +1327,7 @@ namespace mithra {
 
 int64_t sweep_blocks(const RunDev &R, int shape)
 {
-    const int V = R.precision == 32 ? 4 : 2;
-    if (shape >= 8 && R.nx % V != 0)
-        shape = 0;
-    int tx, ty, tz;
-    sweep_shape_dims(shape, &tx, &ty, &tz);
-    if (shape >= 8 && V == 2)
-        ty /= 2;  // FP64 vector tiles: same thread count, half the rows
-    const int64_t ntx = (R.nx + tx - 1) / tx, nty = (R.ny + ty - 1) / ty;
-    const int64_t nch = (R.nz - 2 + tz - 1) / tz;
-    return ntx * nty * nch * 4;
+    return sweep_tiles(R.nx, R.ny, R.nz, R.precision, sweep_effective_shape(R, shape));
 }
 
 template <typename T, int TX, int TY, int TZ>
@@ -1321,24 +1354,24 @@ static hipError_t grp_sweep(const Group &g, int64_t total, int shape, bool lo, h
 {
     constexpr int V = 16 / sizeof(T);
     switch (shape) {
-    case 8: grp_sweep_vec_t<T, V, 128 / V, 512 * V / 128, 32>(g, total, lo, st); break;
-    case 9: grp_sweep_vec_t<T, V, 128 / V, 256 * V / 128, 32>(g, total, lo, st); break;
-    case 10: grp_sweep_vec_t<T, V, 64 / V, 512 * V / 64, 32>(g, total, lo, st); break;
-    case 11: grp_sweep_vec_t<T, V, 128 / V, 512 * V / 128, 16>(g, total, lo, st); break;
-    case 12: grp_sweep_vec_t<T, V, 128 / V, 512 * V / 128, 64>(g, total, lo, st); break;
-    case 13: grp_sweep_vec_t<T, V, 32 / V, 256 * V / 32, 32>(g, total, lo, st); break;
-    case 14: grp_sweep_vec_t<T, V, 128 / V, 256 * V / 128, 16>(g, total, lo, st); break;
-    case 15: grp_sweep_vec_t<T, V, 128 / V, 512 * V / 128, 4>(g, total, lo, st); break;
-    case 16: grp_sweep_vec_t<T, V, 128 / V, 1024 * V / 128, 16>(g, total, lo, st); break;
-    case 17: grp_sweep_vec_t<T, V, 64 / V, 512 * V / 64, 16>(g, total, lo, st); break;
-    case 0: grp_sweep_t<T, 64, 8, 32>(g, total, st); break;
-    case 1: grp_sweep_t<T, 64, 4, 32>(g, total, st); break;
-    case 2: grp_sweep_t<T, 32, 8, 32>(g, total, st); break;
-    case 3: grp_sweep_t<T, 64, 8, 64>(g, total, st); break;
-    case 4: grp_sweep_t<T, 128, 4, 32>(g, total, st); break;
-    case 5: grp_sweep_t<T, 64, 16, 32>(g, total, st); break;
-    case 6: grp_sweep_t<T, 32, 4, 16>(g, total, st); break;
-    case 7: grp_sweep_t<T, 64, 8, 16>(g, total, st); break;
+    case 8: grp_sweep_vec_t<T, V, 16 / V, 256 * V / 16, 4>(g, total, lo, st); break;
+    case 9: grp_sweep_vec_t<T, V, 32 / V, 256 * V / 32, 4>(g, total, lo, st); break;
+    case 10: grp_sweep_vec_t<T, V, 32 / V, 256 * V / 32, 8>(g, total, lo, st); break;
+    case 11: grp_sweep_vec_t<T, V, 32 / V, 256 * V / 32, 16>(g, total, lo, st); break;
+    case 12: grp_sweep_vec_t<T, V, 128 / V, 512 * V / 128, 8>(g, total, lo, st); break;
+    case 13: grp_sweep_vec_t<T, V, 64 / V, 256 * V / 64, 4>(g, total, lo, st); break;
+    case 14: grp_sweep_vec_t<T, V, 64 / V, 256 * V / 64, 8>(g, total, lo, st); break;
+    case 15: grp_sweep_vec_t<T, V, 64 / V, 256 * V / 64, 16>(g, total, lo, st); break;
+    case 16: grp_sweep_vec_t<T, V, 128 / V, 256 * V / 128, 4>(g, total, lo, st); break;
+    case 17: grp_sweep_vec_t<T, V, 128 / V, 256 * V / 128, 16>(g, total, lo, st); break;
+    case 0: grp_sweep_t<T, 64, 4, 16>(g, total, st); break;
+    case 1: grp_sweep_t<T, 64, 4, 4>(g, total, st); break;
+    case 2: grp_sweep_t<T, 32, 8, 4>(g, total, st); break;
+    case 3: grp_sweep_t<T, 64, 4, 8>(g, total, st); break;
+    case 4: grp_sweep_t<T, 32, 8, 8>(g, total, st); break;
+    case 5: grp_sweep_t<T, 64, 8, 32>(g, total, st); break;
+    case 6: grp_sweep_t<T, 32, 8, 16>(g, total, st); break;
+    case 7: grp_sweep_t<T, 16, 16, 4>(g, total, st); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
