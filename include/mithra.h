@@ -291,9 +291,9 @@ int64_t mithra_spectral_power(mithra_handle h, double *dW_domega, int64_t n);
  * ESTATE (after a step). */
 int mithra_set_undulator(mithra_handle h, const mithra_undulator_desc *u);
 
-/* TF/SF seed (see mithra_seed_desc); allowed before the first step.  A
- * seeded run updates the x faces in the boundary kernel (after the
- * injection), not inside the sweep.  Errors: EINVAL, ESTATE. */
+/* TF/SF seed (see mithra_seed_desc); allowed before the first step.  The
+ * injection follows the sweep and corrects the x-face nodes beside it too.
+ * Errors: EINVAL, ESTATE. */
 int mithra_set_seed(mithra_handle h, const mithra_seed_desc *s);
 
 /* Generate n macro-electrons on the device (see mithra_bunch_desc) and

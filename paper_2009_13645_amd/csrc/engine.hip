@@ -997,15 +997,6 @@ extern "C" int mithra_set_seed(mithra_handle h, const mithra_seed_desc *sd)
     R.seed_pol = sd->pol_deg * kPi / 180.0;
     R.seed_w0 = sd->w0;
     R.seed_zf = sd->z_focus;
-    // the injection corrects planes 1 and 2 after the sweep: the x faces on
-    // those planes must then be updated by the boundary kernel, after it
-    if (sweep_fuses_xfaces(R, h->sweep_shape)) {
-        int sh = 0;
-        while (sh < sweep_shape_count() && sweep_fuses_xfaces(R, sh))
-            ++sh;
-        h->sweep_shape = sh;
-    }
-    R.xface_fused = sweep_fuses_xfaces(R, h->sweep_shape);
     drop_graphs(h);
     return MITHRA_OK;
 }
@@ -1154,7 +1145,7 @@ extern "C" int mithra_set_sweep_shape(mithra_handle h, int shape)
     if (h->batched)
         return fail(h, MITHRA_ESTATE, "the run belongs to a batch: its sweep shape is fixed");
     if (h->R.seed_on && sweep_fuses_xfaces(h->R, shape))
-        return fail(h, MITHRA_EINVAL, "a seeded run needs a sweep shape that leaves the x faces to the boundary kernel");
+        return fail(h, MITHRA_EINVAL, "a seeded run takes its default sweep shape or a scalar one");
     h->sweep_shape = shape;
     h->R.xface_fused = sweep_fuses_xfaces(h->R, shape);
     drop_graphs(h);
@@ -1280,7 +1271,7 @@ extern "C" int mithra_autotune_sweep(mithra_handle h, int iters, int *best_shape
         return MITHRA_EINVAL;
     if (!h->loaded)
         return fail(h, MITHRA_ESTATE, "no bunch loaded");
-    if (h->R.seed_on) {  // seeded runs keep their non-fused shape
+    if (h->R.seed_on) {  // seeded runs keep their shape
         if (best_shape)
             *best_shape = h->sweep_shape;
         return MITHRA_OK;
