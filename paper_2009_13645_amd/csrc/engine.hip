@@ -738,7 +738,7 @@ extern "C" int mithra_read_fields(mithra_handle h, int field_id, int dtype, void
     // writes (slot_next; only the A components, phi's are zero for good in a
     // run without space charge).  12 bytes a node and more: it holds the
     // result as FP64 too.
-    char *tmp = (char *)R.pot + (size_t)slot_next(S) * 4 * nn * pf;
+    char *tmp = (char *)R.pot.get() + (size_t)slot_next(S) * 4 * nn * pf;
     if (field_id <= MITHRA_FIELD_BZ) {
         if (S == 0) {
             memset(host_out, 0, bytes);
@@ -748,13 +748,13 @@ extern "C" int mithra_read_fields(mithra_handle h, int field_id, int dtype, void
         src = tmp;
     } else if (field_id <= MITHRA_FIELD_AZ || field_id == MITHRA_FIELD_PHI) {
         const int comp = field_id == MITHRA_FIELD_PHI ? 3 : field_id - MITHRA_FIELD_AX;
-        src = (const char *)R.pot + ((size_t)slot_cur(S) * 4 + comp) * nn * pf;
+        src = (const char *)R.pot.get() + ((size_t)slot_cur(S) * 4 + comp) * nn * pf;
     } else {
         const int comp = field_id == MITHRA_FIELD_RHO ? 3 : field_id - MITHRA_FIELD_JX;
         const size_t o = ((size_t)(S & 1) * 4 + comp) * nn * pf;
-        src = (const char *)R.src + o;
+        src = (const char *)R.src.get() + o;
         if (R.src_lo)
-            lo = (const char *)R.src_lo + o;
+            lo = (const char *)R.src_lo.get() + o;
     }
     if (src != tmp && (lo || esz != pf)) {
         HIPCHK(h, launch_read_convert(R, src, lo, tmp, esz == 8, h->stream));
@@ -1097,7 +1097,7 @@ extern "C" int mithra_generate_bunch(mithra_handle h, const mithra_bunch_desc *b
         const size_t cap = 2 * (size_t)(h->d.max_particles > 0 ? h->d.max_particles : 1);  // sort-key scratch
         if (!(ns >= 1.0) || ns > (double)cap)
             return fail(h, MITHRA_EINVAL, "%.0f shot-noise slices exceed the %zu of the sort scratch", ns, cap);
-        P.counts = (int32_t *)R.sk[0];
+        P.counts = (int32_t *)R.sk[0].get();
         HIPCHK(h, hipMemsetAsync(P.counts, 0, (size_t)ns * 4, h->stream));
         HIPCHK(h, launch_gen_bunch(R, P, 1, zr, h->stream));
         HIPCHK(h, launch_gen_bunch(R, P, 2, zr, h->stream));

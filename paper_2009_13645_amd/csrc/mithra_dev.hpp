@@ -54,6 +54,29 @@ __host__ __device__ inline FastDiv fast_div(uint32_t d) { return FastDiv{d, d ==
 
 __device__ inline uint32_t fdiv(uint32_t t, FastDiv f) { return f.d == 1 ? t : __umulhi(t, f.m); }
 
+// A pointer to device memory inside a descriptor.  Device code reads it as
+// a pointer to the global address space.  In a kernel's own arguments the
+// compiler knows that; of a pointer loaded from a table in memory (the
+// members of a grouped launch) it does not, and every access became a flat
+// instruction, which also occupies the LDS path and makes each wait for LDS
+// wait for memory too (16 runs, 48 steps: 28.9 -> 27.0 ms without them).
+template <typename T>
+struct GlobalPtr {
+#ifdef __HIP_DEVICE_COMPILE__
+    __attribute__((address_space(1))) T *p;
+#else
+    T *p;
+#endif
+    __host__ __device__ T *get() const { return (T *)p; }
+    __host__ __device__ operator T *() const { return get(); }
+    __host__ __device__ T *operator->() const { return get(); }
+    GlobalPtr &operator=(T *q)  // descriptors are filled on the host
+    {
+        p = (decltype(p))q;
+        return *this;
+    }
+};
+
 struct RunDev {
     // mesh
     int nx, ny, nz;
@@ -80,7 +103,7 @@ struct RunDev {
     // spectral power: nfreq frequencies nu = nu_min + (nu_max - nu_min) f / (nfreq - 1) times omega_r
     int nfreq;
     double nu_min, nu_max, omega_r;
-    double *spec;     // [nfreq][8][nx*ny] running transforms (re/im of Ex' Ey' Bx' By')
+    GlobalPtr<double> spec;     // [nfreq][8][nx*ny] running transforms (re/im of Ex' Ey' Bx' By')
     int solver;       // 0 NSFD, 1 FD
     // NSFD interior update: next = a1 cur + a2 (bar_x+ + bar_x-) + a4 (bar_y+ + bar_y-)
     //                              + a6 (cur_k+ + cur_k-) - prev + S
@@ -110,33 +133,33 @@ struct RunDev {
     int ntile[3];
     uint32_t key_inactive;  // sort key of particles outside the active region
     // storage (element type T = float or double for the field arrays)
-    void *pot;        // [3 slots][4 comps][nn]
-    void *src;        // [2 sets][4: Jx Jy Jz rho][nn]
-    void *src_lo;     // compensation terms (same layout) or null
-    void *eb;         // [6: Ex Ey Ez Bx By Bz][nn]
-    double *pr[2][6]; // particle buffers: x y z ux uy uz
-    int32_t *pid[2];
-    uint32_t *key_in;     // sort input: key of rank p of the previous order
-    int32_t *slot_in;     // sort input: the slot that holds it
-    uint32_t *tile_flag;  // per sort tile: the step whose vertex fields the tile's particles gather
+    GlobalPtr<void> pot;        // [3 slots][4 comps][nn]
+    GlobalPtr<void> src;        // [2 sets][4: Jx Jy Jz rho][nn]
+    GlobalPtr<void> src_lo;     // compensation terms (same layout) or null
+    GlobalPtr<void> eb;         // [6: Ex Ey Ez Bx By Bz][nn]
+    GlobalPtr<double> pr[2][6]; // particle buffers: x y z ux uy uz
+    GlobalPtr<int32_t> pid[2];
+    GlobalPtr<uint32_t> key_in;     // sort input: key of rank p of the previous order
+    GlobalPtr<int32_t> slot_in;     // sort input: the slot that holds it
+    GlobalPtr<uint32_t> tile_flag;  // per sort tile: the step whose vertex fields the tile's particles gather
     // per source set and (z plane, y row), [2][nz][ny]: the x range of nodes
     // whose sources the last deposit into the set may have made nonzero,
     // grown by one node along every axis (so that it also covers the
     // neighbour each node-averaged source reads); empty when lo > hi
-    int32_t *srow_lo, *srow_hi;
-    uint32_t *sk[2];
-    int32_t *sv[2];
-    uint32_t *hist;
+    GlobalPtr<int32_t> srow_lo, srow_hi;
+    GlobalPtr<uint32_t> sk[2];
+    GlobalPtr<int32_t> sv[2];
+    GlobalPtr<uint32_t> hist;
     int64_t sort_blocks;
-    int32_t *boxpart;  // per-block partial boxes (load deposit, key pass): [block][8] = lo[3], hi[3], count, pad
-    int32_t *boxslot;  // kBoxSlots x 16 boxes of the per-block push, reduced with atomics (layout: BoxReduceStep)
+    GlobalPtr<int32_t> boxpart;  // per-block partial boxes (load deposit, key pass): [block][8] = lo[3], hi[3], count, pad
+    GlobalPtr<int32_t> boxslot;  // kBoxSlots x 16 boxes of the per-block push, reduced with atomics (layout: BoxReduceStep)
     FastDiv tdiv[3];   // division by the sort tile dims (exact: cell index x tile dim < 2^32)
-    double *ppart;     // partial sums of the plane-power kernel
-    double *power_hist;
+    GlobalPtr<double> ppart;     // partial sums of the plane-power kernel
+    GlobalPtr<double> power_hist;
     int64_t power_cap;
     int k_plane;
     int record_power;
-    Ctl *ctl;
+    GlobalPtr<Ctl> ctl;
 };
 
 // Parameters of the Halton bunch generator (k_particles.hip), filled on the host.
@@ -152,7 +175,7 @@ struct GenParams {
 
 
 // Device address of a Ctl member, formed on the host without dereferencing.
-#define CTL_ADDR(ctl, member) ((int32_t *)((char *)(ctl) + offsetof(::mithra::Ctl, member)))
+#define CTL_ADDR(ctl, member) ((int32_t *)((char *)(ctl).get() + offsetof(::mithra::Ctl, member)))
 
 __host__ __device__ inline int64_t nid(const RunDev &R, int i, int j, int k)
 {
@@ -162,19 +185,19 @@ __host__ __device__ inline int64_t nid(const RunDev &R, int i, int j, int k)
 template <typename T>
 __device__ inline T *pot_ptr(const RunDev &R, int slot, int comp)
 {
-    return reinterpret_cast<T *>(R.pot) + ((int64_t)slot * 4 + comp) * R.nn;
+    return static_cast<T *>(R.pot.get()) + ((int64_t)slot * 4 + comp) * R.nn;
 }
 
 template <typename T>
 __device__ inline T *src_ptr(const RunDev &R, int set, int comp)
 {
-    return reinterpret_cast<T *>(R.src) + ((int64_t)set * 4 + comp) * R.nn;
+    return static_cast<T *>(R.src.get()) + ((int64_t)set * 4 + comp) * R.nn;
 }
 
 template <typename T>
 __device__ inline T *srclo_ptr(const RunDev &R, int set, int comp)
 {
-    return reinterpret_cast<T *>(R.src_lo) + ((int64_t)set * 4 + comp) * R.nn;
+    return static_cast<T *>(R.src_lo.get()) + ((int64_t)set * 4 + comp) * R.nn;
 }
 
 // V consecutive values moved as one 16-byte access when sizeof(T) V == 16.
@@ -217,7 +240,7 @@ __device__ inline void vstore(T *p, const Vec<T, V> &a)
 template <typename T>
 __device__ inline T *eb_node(const RunDev &R, int64_t n)
 {
-    return reinterpret_cast<T *>(R.eb) + 8 * n;
+    return static_cast<T *>(R.eb.get()) + 8 * n;
 }
 
 // Time-level slots of the three rotating potential arrays during step s:
