@@ -66,7 +66,7 @@ int64_t power_blocks();
 hipError_t launch_power_group(const Group &g, int64_t total, const Group &gf, int64_t total_f, int precision,
                               hipStream_t st);
 hipError_t launch_vertex_power(const RunDev &R, hipStream_t st);
-hipError_t launch_push_group(const Group &g, int64_t total, int precision, int compensated, hipStream_t st);
+hipError_t launch_push_group(const Group &g, int64_t total, int precision, int compensated, bool subs, hipStream_t st);
 hipError_t launch_box_group(const Group &g, int64_t total, hipStream_t st);
 hipError_t launch_sort_group(const Group &gs, int64_t total_s, const Group &gd, int64_t total_d, const Group &gp,
                              int64_t total_p, int max_passes, hipStream_t st);
@@ -357,10 +357,20 @@ extern "C" int mithra_init_grid(const mithra_grid_desc *d, void *dev_arena, size
     R.Lu = d->n_periods * d->lambda_u;
     R.z_ent = d->z_entrance;
     R.theta = d->pol_angle_deg * kPi / 180.0;
+    R.sth = std::sin(R.theta);
+    R.cth = std::cos(R.theta);
+    R.half_turns = 2.0 / d->lambda_u;
+    R.gbc = R.gamma0 * R.beta0 * kC;
+    R.b0c = R.beta0 * kC;
+    R.ek = kQe * R.dtb / (2.0 * kMe * kC);
+    R.ak = -kQe * R.dtb / (2.0 * kMe);
+    R.cdtb = kC * R.dtb;
+    R.B_per_K = 2.0 * kPi * kMe * kC / (kQe * d->lambda_u);
     R.und_type = d->und_type;
     R.Kund = d->K;
     R.lam_u = d->lambda_u;
     R.n_modules = 1;
+    R.inv_pitch = 1.0 / R.Lu;
     R.und_ext = d->und_type >= 2 ? 1 : 0;
     // NSFD: A = 0.25 (1 + 0.02 / ((dz/dx)^2 + (dz/dy)^2)); r_l = c dt / d_l
     const double cdt = kC * R.dt;
@@ -953,6 +963,8 @@ extern "C" int mithra_set_undulator(mithra_handle h, const mithra_undulator_desc
     R.n_modules = u->n_modules;
     R.gap = u->gap;
     R.dK = u->dK;
+    R.inv_pitch = 1.0 / (R.Lu + R.gap);
+    R.inv_gap = R.gap > 0.0 ? 1.0 / R.gap : 0.0;  // a single module has no gap
     R.opt_signal = u->signal;
     R.opt_ctau = u->ctau;
     R.opt_ct0 = u->ct0;
@@ -1370,7 +1382,7 @@ struct mithra_batch_s {
         GroupTab t;
     };
     std::vector<SweepCls> sweep;
-    GroupTab mur[2], mur_edge[2], vertex[2], power[2], power_final[2], push[3], one, sort_s, sort_d, sort_p;
+    GroupTab mur[2], mur_edge[2], vertex[2], power[2], power_final[2], push[6], one, sort_s, sort_d, sort_p;
     int max_passes = 0;
     hipGraphExec_t graph = nullptr;         // one batched step
     hipGraphExec_t graph_nosort = nullptr;  // the same without the sort passes (captured on first use)
@@ -1410,7 +1422,7 @@ extern "C" size_t mithra_batch_workspace_bytes(int32_t n_runs)
     const size_t n = (size_t)n_runs;
     // every stage kind holds each member at most once; sweep classes add at
     // most one table per member
-    return 11 * tab_bytes(n) + (n + 18) * 3 * 256 + 256;
+    return 11 * tab_bytes(n) + (n + 21) * 3 * 256 + 256;
 }
 
 // table of members `mem` (indices into b->runs), nb(member) workgroups each
@@ -1491,12 +1503,12 @@ static int build_tables(mithra_batch b)
         if (rc)
             return rc;
     }
-    for (int ci = 0; ci < 3; ++ci) {  // FP64, FP32, FP32 compensated
+    for (int ci = 0; ci < 6; ++ci) {  // FP64, FP32, FP32 compensated; the same with sub-steps
         std::vector<int> mem;
         for (int i = 0; i < n; ++i) {
             const RunDev &R = b->runs[i]->R;
             const int c = R.precision == 64 ? 0 : (R.compensated ? 2 : 1);
-            if (c == ci)
+            if (c + (R.n_sub > 1 ? 3 : 0) == ci)
                 mem.push_back(i);
         }
         int rc = make_tab(b, mem, [](const RunDev &R) { return dep_blocks(R.np); }, &b->push[ci]);
@@ -1551,9 +1563,9 @@ static int enqueue_batch_step(mithra_batch b, hipStream_t st, bool sort)
         // the plane power reads the potentials of this step only
         BHIPCHK(b, launch_power_group(b->power[pi].g, b->power[pi].total, b->power_final[pi].g,
                                       b->power_final[pi].total, prec, cs));
-        for (int ci = 0; ci < 3; ++ci)
-            if ((ci == 0) == (chain == 0))
-                BHIPCHK(b, launch_push_group(b->push[ci].g, b->push[ci].total, ci == 0 ? 64 : 32, ci == 2, cs));
+        for (int ci = 0; ci < 6; ++ci)
+            if ((ci % 3 == 0) == (chain == 0))
+                BHIPCHK(b, launch_push_group(b->push[ci].g, b->push[ci].total, prec, ci % 3 == 2, ci >= 3, cs));
     }
     BHIPCHK(b, hipEventRecord(b->join, b->side));
     BHIPCHK(b, hipStreamWaitEvent(st, b->join, 0));

@@ -23,18 +23,20 @@ constexpr int kLdsNodes = 1650;
 // The block's deposits are summed in LDS over its node box when the box
 // fits, then added to HBM once per touched node; otherwise directly.
 // EXT selects the general external field (undulator arrays, optical
-// undulators); the single static module keeps its own path.
-template <typename T, bool COMP, int MODE, bool EXT = false>
+// undulators); the single static module keeps its own path.  SUBS: several
+// sub-steps.  In a loop over them the compiler keeps the field's polynomial
+// constants in registers across the whole push (161 VGPRs, 227 with the
+// general field), so runs of one sub-step, the usual case, have their own
+// body without it (124-154).
+template <typename T, bool COMP, int MODE, bool EXT = false, bool SUBS = false>
 struct PushDeposit {
     // The block's box accumulates in FP64 LDS whatever the source precision
     // (an FP32 box measured 367 against 225 us per launch at the FEL
-    // amplifier).  Three waves per SIMD: the push needs about 160 VGPRs (at
-    // 128 it spills), and the box allows three blocks per CU.  The general
-    // external field (arrays, optical undulators) needs about 210: two
-    // waves, where three spilled about 50 registers per lane.
+    // amplifier).  Three waves per SIMD: the box allows three blocks per CU.
+    // Sub-steps of the general external field need about 227 registers: two.
     using LT = double;
     static constexpr int kThreads = kDepThreads;
-    static constexpr int kWaves = EXT ? 2 : 3;
+    static constexpr int kWaves = EXT && SUBS ? 2 : 3;
     static __device__ void run(const RunDev &R, Blk blk)
     {
         __shared__ LT lds[4 * kLdsNodes];
@@ -110,18 +112,23 @@ struct PushDeposit {
                             }
                 }
                 const double t_half = ((double)s + 0.5) * R.dt;
-                for (int sub = 0; sub < R.n_sub; ++sub) {
+                auto sub_step = [&](double t) {
                     double Ee[3], Be[3];
-                    external_field<EXT>(R, r[0], r[1], r[2], t_half + (double)sub * R.dtb, Ee, Be);
+                    external_field<EXT>(R, r[0], r[1], r[2], t, Ee, Be);
                     for (int a = 0; a < 3; ++a) {
                         Ee[a] += Eg[a];
                         Be[a] += Bg[a];
                     }
-                    boris(u, Ee, Be, R.dtb);
-                    const double ig = 1.0 / sqrt(1.0 + u[0] * u[0] + u[1] * u[1] + u[2] * u[2]);
+                    boris(R, u, Ee, Be);
+                    const double ig = rsqrt(1.0 + u[0] * u[0] + u[1] * u[1] + u[2] * u[2]);
                     for (int a = 0; a < 3; ++a)
-                        r[a] = r[a] + kC * R.dtb * u[a] * ig;
-                }
+                        r[a] = r[a] + R.cdtb * u[a] * ig;
+                };
+                if constexpr (SUBS)
+                    for (int sub = 0; sub < R.n_sub; ++sub)
+                        sub_step(t_half + (double)sub * R.dtb);
+                else
+                    sub_step(t_half);
                 // the pushed state goes to the other buffer in sort order
                 const int nb = pb ^ 1;
                 for (int a = 0; a < 3; ++a) {
@@ -470,26 +477,24 @@ static hipError_t launch_dep(const RunDev &R, hipStream_t st)
     if constexpr (MODE == 0) {
         // a step's push, then the Mur edge and corner workgroups
         const unsigned blocks = (unsigned)((R.np + kDepThreads - 1) / kDepThreads + mur_edge_blocks_of(R));
-        if (R.und_ext) {
+        auto go = [&](auto ext, auto subs) {
+            constexpr bool X = decltype(ext)::value, S = decltype(subs)::value;
             if (R.precision == 64)
-                hipLaunchKernelGGL((k_run<PushThenEdges<PushDeposit<double, false, 0, true>, double>>), dim3(blocks),
+                hipLaunchKernelGGL((k_run<PushThenEdges<PushDeposit<double, false, 0, X, S>, double>>), dim3(blocks),
                                    dim3(kDepThreads), 0, st, R);
             else if (R.compensated)
-                hipLaunchKernelGGL((k_run<PushThenEdges<PushDeposit<float, true, 0, true>, float>>), dim3(blocks),
+                hipLaunchKernelGGL((k_run<PushThenEdges<PushDeposit<float, true, 0, X, S>, float>>), dim3(blocks),
                                    dim3(kDepThreads), 0, st, R);
             else
-                hipLaunchKernelGGL((k_run<PushThenEdges<PushDeposit<float, false, 0, true>, float>>), dim3(blocks),
+                hipLaunchKernelGGL((k_run<PushThenEdges<PushDeposit<float, false, 0, X, S>, float>>), dim3(blocks),
                                    dim3(kDepThreads), 0, st, R);
-        } else if (R.precision == 64) {
-            hipLaunchKernelGGL((k_run<PushThenEdges<PushDeposit<double, false, 0>, double>>), dim3(blocks),
-                               dim3(kDepThreads), 0, st, R);
-        } else if (R.compensated) {
-            hipLaunchKernelGGL((k_run<PushThenEdges<PushDeposit<float, true, 0>, float>>), dim3(blocks),
-                               dim3(kDepThreads), 0, st, R);
-        } else {
-            hipLaunchKernelGGL((k_run<PushThenEdges<PushDeposit<float, false, 0>, float>>), dim3(blocks),
-                               dim3(kDepThreads), 0, st, R);
-        }
+        };
+        const std::true_type yes;
+        const std::false_type no;
+        if (R.und_ext)
+            R.n_sub > 1 ? go(yes, yes) : go(yes, no);
+        else
+            R.n_sub > 1 ? go(no, yes) : go(no, no);
         return hipGetLastError();
     } else {
         // the load's deposit (no push, no boundary)
@@ -594,16 +599,24 @@ hipError_t launch_bunching(const RunDev &R, double *part, int blocks, hipStream_
 // ---------------------------------------------------------------------------
 namespace mithra {
 
-hipError_t launch_push_group(const Group &g, int64_t total, int precision, int compensated, hipStream_t st)
+// members of one precision, compensation and sub-step variant
+hipError_t launch_push_group(const Group &g, int64_t total, int precision, int compensated, bool subs, hipStream_t st)
 {
     if (total <= 0)
         return hipSuccess;
-    if (precision == 64)
-        hipLaunchKernelGGL((k_group<PushDeposit<double, false, 0>>), dim3((unsigned)total), dim3(kDepThreads), 0, st, g);
-    else if (compensated)
-        hipLaunchKernelGGL((k_group<PushDeposit<float, true, 0>>), dim3((unsigned)total), dim3(kDepThreads), 0, st, g);
-    else
-        hipLaunchKernelGGL((k_group<PushDeposit<float, false, 0>>), dim3((unsigned)total), dim3(kDepThreads), 0, st, g);
+    auto go = [&](auto s) {
+        constexpr bool S = decltype(s)::value;
+        if (precision == 64)
+            hipLaunchKernelGGL((k_group<PushDeposit<double, false, 0, false, S>>), dim3((unsigned)total),
+                               dim3(kDepThreads), 0, st, g);
+        else if (compensated)
+            hipLaunchKernelGGL((k_group<PushDeposit<float, true, 0, false, S>>), dim3((unsigned)total),
+                               dim3(kDepThreads), 0, st, g);
+        else
+            hipLaunchKernelGGL((k_group<PushDeposit<float, false, 0, false, S>>), dim3((unsigned)total),
+                               dim3(kDepThreads), 0, st, g);
+    };
+    subs ? go(std::true_type{}) : go(std::false_type{});
     return hipGetLastError();
 }
 

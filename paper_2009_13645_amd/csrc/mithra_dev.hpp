@@ -82,19 +82,24 @@ struct RunDev {
     int nx, ny, nz;
     int64_t nn;
     double dx, dy, dz, x0, y0, z0;
-    double inv_dx, inv_dy, inv_dz;  // only used where a product is not compared bitwise
+    double inv_dx, inv_dy, inv_dz;  // rounded reciprocals (see quotient)
     // time
     double dt, dtb;
     int n_sub;
     int sort_every;  // sort after every sort_every-th push (>= 1)
     // frame and undulator
     double gamma0, beta0;
-    double ku, B0, Lu, z_ent, theta;
+    double ku, B0, Lu, z_ent;
+    double theta, sth, cth;        // polarisation angle, its sine and cosine
+    double half_turns;             // 2 / lambda_u: undulator phase in half turns per metre
+    double gbc, b0c;               // gamma0 beta0 c, beta0 c
+    double ek, ak, cdtb;           // Boris: e dt_b / (2 m c), -e dt_b / (2 m); c dt_b
     int und_type;     // 0 planar, 1 helical, 2 optical plane wave, 3 optical Gaussian beam
     int und_ext;      // 1: the external field needs the general path (arrays or optical)
     double Kund, lam_u; // undulator parameter (optical: a0) and period (optical: half the wavelength)
     int n_modules;    // static array: modules, K_m = K + m dK, gaps between them
     double gap, dK;
+    double B_per_K, inv_pitch, inv_gap;  // B0 / K, 1 / (module + gap), 1 / gap
     int opt_signal;   // optical pulse: signal type, length, offset (c t, lab), CEP (rad)
     double opt_ctau, opt_ct0, opt_cep, opt_w0[2], opt_zf;
     // TF/SF seed (planes k = 1 and 2)

@@ -15,18 +15,45 @@
 
 namespace mithra {
 
+// The push is short of VALU issue, so it avoids what the
+// compiler expands at length: an FP64 division (11 instructions), sincos of
+// an argument that may need a many-word reduction (its code and registers
+// are there for every particle), and arithmetic on values that are the same
+// for the whole run (R.gbc, R.ek and so on come from the host).
+
+// 1 / x for a normal x: the hardware estimate and two Newton steps (relative
+// error below 1.5 x 2^-53, one rounding more than the division's).
+__device__ inline double recip(double x)
+{
+    double r = __builtin_amdgcn_rcp(x);
+    r = fma(r, fma(-x, r, 1.0), r);
+    return fma(r, fma(-x, r, 1.0), r);
+}
+
+// a / b rounded as the division rounds it, from y = 1 / b rounded to FP64:
+// the first correction makes the quotient faithful, and the correction of a
+// faithful quotient by a correctly rounded reciprocal gives the rounded one
+// (Markstein's theorem).  For quotients in the range of grid coordinates;
+// where a is not finite it is NaN, which no cell test accepts either.
+__device__ inline double quotient(double a, double b, double y)
+{
+    double q = a * y;
+    q = fma(fma(-q, b, a), y, q);
+    return fma(fma(-q, b, a), y, q);
+}
+
 __device__ inline void cosh_sinh(double x, double &ch, double &sh)
 {
-    const double em = expm1(x);
-    const double inv = 1.0 / (1.0 + em);
-    sh = 0.5 * em * (2.0 + em) * inv;
-    ch = 1.0 + 0.5 * em * em * inv;
+    const double em = expm1(fabs(x));
+    const double h = 0.5 * em * recip(1.0 + em);
+    sh = copysign(h * (2.0 + em), x);
+    ch = fma(h, em, 1.0);
 }
 
 // longitudinal profile of the planar pattern at lab z': (g, h) multiply
 // cosh / sinh of the transverse argument for the transverse / longitudinal
 // field: periodic body, fringe before the entrance and (mirrored) after
-// the exit
+// the exit.  The body's phase in half turns: sincospi reduces it exactly.
 __device__ inline void profile(const RunDev &R, double zl, double &g, double &h)
 {
     if (zl < 0.0 || zl > R.Lu) {
@@ -35,20 +62,20 @@ __device__ inline void profile(const RunDev &R, double zl, double &g, double &h)
         g = a * e;
         h = e;
     } else {
-        sincos(R.ku * zl, &g, &h);
+        sincospi(zl * R.half_turns, &g, &h);
     }
 }
 
 __device__ inline void undulator_field(const RunDev &R, double x, double y, double z, double t, double E[3],
                                        double B[3])
 {
-    const double zl = R.gamma0 * (z - R.z_ent + R.beta0 * kC * t);
+    const double zl = R.gamma0 * (z - R.z_ent + R.b0c * t);
     double Bl[3];
     if (R.und_type == 1) {
         // planar pattern along y at z' plus planar pattern along x at
         // z' + lambda_u/4; inside the magnet the second profile is the
         // first shifted by a quarter period: (g, h) -> (h, -g)
-        const double zq = zl + 0.25 * (2.0 * kPi / R.ku);
+        const double zq = zl + 0.25 * R.lam_u;
         double g1, h1, g2, h2;
         profile(R, zl, g1, h1);
         if (zq >= 0.0 && zq <= R.Lu && zl >= 0.0) {
@@ -64,18 +91,16 @@ __device__ inline void undulator_field(const RunDev &R, double x, double y, doub
         Bl[1] = R.B0 * chy * g1;
         Bl[2] = R.B0 * (shy * h1 + shx * h2);
     } else {
-        double sth, cth, g, h, ch, sh;
-        sincos(R.theta, &sth, &cth);
+        double g, h, ch, sh;
         profile(R, zl, g, h);
-        cosh_sinh(R.ku * (x * sth + y * cth), ch, sh);
+        cosh_sinh(R.ku * (x * R.sth + y * R.cth), ch, sh);
         const double bp = R.B0 * ch * g;
-        Bl[0] = bp * sth;
-        Bl[1] = bp * cth;
+        Bl[0] = bp * R.sth;
+        Bl[1] = bp * R.cth;
         Bl[2] = R.B0 * sh * h;
     }
-    const double gbc = R.gamma0 * R.beta0 * kC;
-    E[0] = -gbc * Bl[1];
-    E[1] = gbc * Bl[0];
+    E[0] = -R.gbc * Bl[1];
+    E[1] = R.gbc * Bl[0];
     E[2] = 0.0;
     B[0] = R.gamma0 * Bl[0];
     B[1] = R.gamma0 * Bl[1];
@@ -86,10 +111,10 @@ __device__ inline void undulator_field(const RunDev &R, double x, double y, doub
 
 // window of the gap fringes of an undulator array: 1 at the module edge,
 // ~6e-5 at the far end of the gap
-__device__ inline double gap_window(double dz, double g)
+__device__ inline double gap_window(double dz, double inv_g)
 {
-    const double t = kPi * dz / g;
-    return 0.35875 + 0.48829 * cos(t) + 0.14128 * cos(2.0 * t) + 0.01168 * cos(3.0 * t);
+    const double c = cospi(dz * inv_g);
+    return 0.35875 + 0.48829 * c + 0.14128 * (2.0 * c * c - 1.0) + 0.01168 * ((4.0 * c * c - 3.0) * c);
 }
 
 // longitudinal profile of the planar pattern of a module array at lab z'
@@ -100,45 +125,46 @@ __device__ inline void array_profile(const RunDev &R, double zl, double &gB, dou
 {
     const int M = R.n_modules;
     const double pitch = R.Lu + R.gap;
-    int m = (int)floor(zl / pitch);
+    int m = (int)floor(zl * R.inv_pitch);
     m = m < 0 ? 0 : (m > M - 1 ? M - 1 : m);
+    // floor of the rounded product may be one off at a module's entrance
+    if (m > 0 && zl < m * pitch)
+        --m;
+    else if (m < M - 1 && zl >= (m + 1) * pitch)
+        ++m;
     const double ent = m * pitch, ext = ent + R.Lu;
-    const double b0 = 2.0 * kPi * kMe * kC * (R.Kund + m * R.dK) / (kQe * R.lam_u);
+    const double b0 = R.B_per_K * (R.Kund + m * R.dK);
     if (zl >= ent && zl <= ext) {
-        gB = b0 * sin(R.ku * (zl - ent));
-        hB = b0 * cos(R.ku * (zl - ent));
+        sincospi((zl - ent) * R.half_turns, &gB, &hB);
+        gB *= b0;
+        hB *= b0;
         return;
     }
-    if (zl < ent) {
-        const double a = R.ku * (zl - ent), e = exp(-0.5 * a * a);
-        gB = b0 * (a * e);
-        hB = b0 * e;
+    // fringe before the first module, after the last one, or of the module
+    // before a gap
+    const double a1 = R.ku * (zl - (zl < ent ? ent : ext)), e1 = exp(-0.5 * a1 * a1);
+    gB = b0 * (a1 * e1);
+    hB = b0 * e1;
+    if (zl < ent || m == M - 1)
         return;
-    }
-    const double a1 = R.ku * (zl - ext), e1 = exp(-0.5 * a1 * a1);
-    if (m == M - 1) {
-        gB = b0 * (a1 * e1);
-        hB = b0 * e1;
-        return;
-    }
     const double ent2 = (m + 1) * pitch;
-    const double b1 = 2.0 * kPi * kMe * kC * (R.Kund + (m + 1) * R.dK) / (kQe * R.lam_u);
+    const double b1 = R.B_per_K * (R.Kund + (m + 1) * R.dK);
     const double a2 = R.ku * (zl - ent2), e2 = exp(-0.5 * a2 * a2);
-    const double f1 = gap_window(zl - ext, R.gap), f2 = gap_window(ent2 - zl, R.gap);
-    gB = b0 * (a1 * e1) * f1 + b1 * (a2 * e2) * f2;
-    hB = b0 * e1 * f1 + b1 * e2 * f2;
+    const double f1 = gap_window(zl - ext, R.inv_gap), f2 = gap_window(ent2 - zl, R.inv_gap);
+    gB = gB * f1 + b1 * (a2 * e2) * f2;
+    hB = hB * f1 + b1 * e2 * f2;
 }
 
-__device__ inline void array_planar(const RunDev &R, double x, double y, double zl, double th, double Bl[3])
+// the planar pattern along (sth, cth)
+__device__ inline void array_planar(const RunDev &R, double x, double y, double zl, double sth, double cth,
+                                    double Bl[3])
 {
-    double gB, hB, sth, cth;
+    double gB, hB, ch, sh;
     array_profile(R, zl, gB, hB);
-    sincos(th, &sth, &cth);
-    const double eta = x * sth + y * cth;
-    const double Bperp = gB * cosh(R.ku * eta);
-    Bl[0] = Bperp * sth;
-    Bl[1] = Bperp * cth;
-    Bl[2] = hB * sinh(R.ku * eta);
+    cosh_sinh(R.ku * (x * sth + y * cth), ch, sh);
+    Bl[0] = gB * ch * sth;
+    Bl[1] = gB * ch * cth;
+    Bl[2] = hB * sh;
 }
 
 // optical pulse signature with unit amplitude (modulated Neumann scaled by
@@ -221,14 +247,12 @@ __device__ inline void undulator_field_ext(const RunDev &R, double x, double y, 
         optical_lab(R, x, y, zl, tl, El, Bl);
     } else if (R.und_type == 1) {
         double tmp[3];
-        array_planar(R, x, y, zl, 0.0, tmp);
-        for (int a = 0; a < 3; ++a)
-            Bl[a] += tmp[a];
-        array_planar(R, x, y, zl + 0.25 * R.lam_u, 0.5 * kPi, tmp);
+        array_planar(R, x, y, zl, 0.0, 1.0, Bl);
+        array_planar(R, x, y, zl + 0.25 * R.lam_u, 1.0, 0.0, tmp);
         for (int a = 0; a < 3; ++a)
             Bl[a] += tmp[a];
     } else {
-        array_planar(R, x, y, zl, R.theta, Bl);
+        array_planar(R, x, y, zl, R.sth, R.cth, Bl);
     }
     E[0] = g0 * (El[0] + kC * b0 * (-Bl[1]));
     E[1] = g0 * (El[1] + kC * b0 * (Bl[0]));
@@ -250,30 +274,30 @@ __device__ inline void external_field(const RunDev &R, double x, double y, doubl
         undulator_field(R, x, y, z, t, E, B);
 }
 
-__device__ inline void boris(double u[3], const double E[3], const double B[3], double dtb)
+__device__ inline void boris(const RunDev &R, double u[3], const double E[3], const double B[3])
 {
-    const double ek = kQe * dtb / (2.0 * kMe * kC);
     double t1[3];
     for (int a = 0; a < 3; ++a)
-        t1[a] = u[a] - ek * E[a];
-    const double alpha = -kQe * dtb / (2.0 * kMe * sqrt(1.0 + t1[0] * t1[0] + t1[1] * t1[1] + t1[2] * t1[2]));
+        t1[a] = u[a] - R.ek * E[a];
+    const double alpha = R.ak * rsqrt(1.0 + t1[0] * t1[0] + t1[1] * t1[1] + t1[2] * t1[2]);
     double t2[3];
     t2[0] = t1[0] + alpha * (t1[1] * B[2] - t1[2] * B[1]);
     t2[1] = t1[1] + alpha * (t1[2] * B[0] - t1[0] * B[2]);
     t2[2] = t1[2] + alpha * (t1[0] * B[1] - t1[1] * B[0]);
-    const double f = 2.0 * alpha / (1.0 + alpha * alpha * (B[0] * B[0] + B[1] * B[1] + B[2] * B[2]));
+    const double f = 2.0 * alpha * recip(1.0 + alpha * alpha * (B[0] * B[0] + B[1] * B[1] + B[2] * B[2]));
     const double s[3] = {f * B[0], f * B[1], f * B[2]};
-    u[0] = t1[0] + (t2[1] * s[2] - t2[2] * s[1]) - ek * E[0];
-    u[1] = t1[1] + (t2[2] * s[0] - t2[0] * s[2]) - ek * E[1];
-    u[2] = t1[2] + (t2[0] * s[1] - t2[1] * s[0]) - ek * E[2];
+    u[0] = t1[0] + (t2[1] * s[2] - t2[2] * s[1]) - R.ek * E[0];
+    u[1] = t1[1] + (t2[2] * s[0] - t2[0] * s[2]) - R.ek * E[1];
+    u[2] = t1[2] + (t2[0] * s[1] - t2[1] * s[0]) - R.ek * E[2];
 }
 
 // grid coordinates and active cell (1 <= cell <= n-3 on every axis)
 __device__ inline bool cell_of(const RunDev &R, const double r[3], double g[3], int c[3])
 {
-    g[0] = (r[0] - R.x0) / R.dx;
-    g[1] = (r[1] - R.y0) / R.dy;
-    g[2] = (r[2] - R.z0) / R.dz;
+    // the rounded quotients, so that the cells are those of the division
+    g[0] = quotient(r[0] - R.x0, R.dx, R.inv_dx);
+    g[1] = quotient(r[1] - R.y0, R.dy, R.inv_dy);
+    g[2] = quotient(r[2] - R.z0, R.dz, R.inv_dz);
     const int n[3] = {R.nx, R.ny, R.nz};
     bool ok = true;
 #pragma unroll
