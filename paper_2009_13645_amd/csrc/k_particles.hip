@@ -39,23 +39,24 @@ struct PushDeposit {
     static constexpr int kWaves = EXT && SUBS ? 2 : 3;
     static __device__ void run(const RunDev &R, Blk blk)
     {
-        __shared__ LT lds[4 * kLdsNodes];
-        __shared__ int bb[7];  // node box lo[3], hi[3]; active count
+        constexpr int kWavesPerBlock = kDepThreads / 64;
+        __shared__ __attribute__((aligned(16))) LT lds[4 * kLdsNodes];
+        __shared__ __attribute__((aligned(16))) int wbox[kWavesPerBlock][8];  // per wavefront: node box lo[3], hi[3]; active count
         const int64_t s = R.ctl->step;
         const int pb = R.ctl->pbuf;
         const int set = MODE == 0 ? (int)((s + 1) & 1) : 0;
         const int64_t p = (int64_t)blk.id * blockDim.x + threadIdx.x;
-        if (threadIdx.x < 3) {
-            bb[threadIdx.x] = 0x7fffffff;
-            bb[3 + threadIdx.x] = -1;
-        }
-        if (threadIdx.x == 3)
-            bb[6] = 0;
-
         double g1[3] = {0, 0, 0}, g2[3] = {0, 0, 0};
         int c1[3] = {0, 0, 0}, c2[3] = {0, 0, 0};
         bool dep_j = false, dep_q = false;
-        if (p < R.np) {
+        auto clear_box = [&] {
+            static_assert(4 * kLdsNodes * sizeof(LT) % 16 == 0, "cleared in 16-byte words");
+            for (int e = threadIdx.x; e < (int)(4 * kLdsNodes * sizeof(LT) / 16); e += kDepThreads)
+                reinterpret_cast<uint4 *>(lds)[e] = make_uint4(0, 0, 0, 0);
+        };
+        if (p >= R.np) {
+            clear_box();
+        } else {
             // rank p of the last sort: the slot where the previous push (or
             // the load) left the particle, and its id
             const int sb = R.ctl->sorted_buf;
@@ -66,6 +67,11 @@ struct PushDeposit {
                 r[a] = R.pr[pb][a][src];
                 u[a] = R.pr[pb][3 + a][src];
             }
+            // the box is cleared while the state is on its way (cleared after
+            // the box reduction, for its extent only, with one more barrier:
+            // 159 against 155 us a launch at the FEL amplifier); the size of
+            // the block's box is not known yet, so all of it
+            clear_box();
             if (MODE == 1) {
                 const double ig = 1.0 / sqrt(1.0 + u[0] * u[0] + u[1] * u[1] + u[2] * u[2]);
                 double r0[3];
@@ -167,31 +173,44 @@ struct PushDeposit {
         }
         // active particles after the push (sort statistics)
         const int nact = MODE == 0 ? (int)__popcll(__ballot(dep_q)) : 0;
-        __syncthreads();
         if ((threadIdx.x & 63) == 0) {
-            if (hi[0] >= 0)
-                for (int l = 0; l < 3; ++l) {
-                    atomicMin(&bb[l], lo[l]);
-                    atomicMax(&bb[3 + l], hi[l]);
-                }
-            if (nact != 0)
-                atomicAdd(&bb[6], nact);
+            int *w = wbox[threadIdx.x >> 6];
+            for (int l = 0; l < 3; ++l) {
+                w[l] = lo[l];
+                w[3 + l] = hi[l];
+            }
+            w[6] = nact;
         }
         __syncthreads();
+        // the block's box from its wavefronts' (the same in every thread)
+        int bb[7] = {0x7fffffff, 0x7fffffff, 0x7fffffff, -1, -1, -1, 0};
+    #pragma unroll
+        for (int w = 0; w < kWavesPerBlock; ++w) {
+            const int4 q0 = *(const int4 *)&wbox[w][0], q1 = *(const int4 *)&wbox[w][4];
+            bb[0] = min(bb[0], q0.x);
+            bb[1] = min(bb[1], q0.y);
+            bb[2] = min(bb[2], q0.z);
+            bb[3] = max(bb[3], q0.w);
+            bb[4] = max(bb[4], q1.x);
+            bb[5] = max(bb[5], q1.y);
+            bb[6] += q1.z;
+        }
+    #pragma unroll
+        for (int a = 0; a < 7; ++a)
+            bb[a] = __builtin_amdgcn_readfirstlane(bb[a]);
         // this block's box: the push reduces it into its slot (BoxReduceStep),
         // the load deposit writes its partial (k_box_reduce)
         if (MODE == 0) {
             int32_t *slot = R.boxslot + 16 * (blk.id & (kBoxSlots - 1));
-            if (threadIdx.x < 6 && bb[3] >= 0) {
-                if (threadIdx.x < 3)
-                    atomicMin(&slot[threadIdx.x], bb[threadIdx.x]);
-                else
-                    atomicMax(&slot[threadIdx.x], bb[threadIdx.x]);
-            } else if (threadIdx.x == 6 && bb[6] != 0) {
+            if (threadIdx.x < 3 && bb[3] >= 0)
+                atomicMin(&slot[threadIdx.x], threadIdx.x == 0 ? bb[0] : (threadIdx.x == 1 ? bb[1] : bb[2]));
+            else if (threadIdx.x < 6 && bb[3] >= 0)
+                atomicMax(&slot[threadIdx.x], threadIdx.x == 3 ? bb[3] : (threadIdx.x == 4 ? bb[4] : bb[5]));
+            else if (threadIdx.x == 6 && bb[6] != 0)
                 atomicAdd(&slot[12], bb[6]);
-            }
-        } else if (threadIdx.x < 7) {
-            R.boxpart[8 * (int64_t)blk.id + threadIdx.x] = threadIdx.x < 6 ? bb[threadIdx.x] : 0;
+        } else if (threadIdx.x == 0) {
+            for (int a = 0; a < 7; ++a)
+                R.boxpart[8 * (int64_t)blk.id + a] = a < 6 ? bb[a] : 0;
         }
         const int L0 = bb[0], L1 = bb[1], L2 = bb[2];
         if (bb[3] < 0)
@@ -213,16 +232,13 @@ struct PushDeposit {
         const int ex = bb[3] - L0 + 1, ey = bb[4] - L1 + 1, ez = bb[5] - L2 + 1;
         const int vol = ex * ey * ez;
         const GlobalAcc<T, COMP> gacc = make_gacc<T, COMP>(R, set);
-        // Zero an LDS box, deposit into it, then flush its nonzero nodes with
+        // Deposit into a cleared LDS box, then flush its nonzero nodes with
         // global atomics: one node per thread per round, its four components
         // together (so that the returning atomics of the compensated mode are
         // in flight together), the node's (i, j, k) decoded once for the four.
-        // first / stride: this thread's share; sync orders the three phases.
+        // first / stride: this thread's share; sync orders the two phases.
         auto lds_deposit = [&](LT *base, int B0, int B1, int B2, int bx, int by, int bv, int first, int stride,
                                auto sync) {
-            for (int e = first; e < 4 * bv; e += stride)
-                base[e] = (LT)0;
-            sync();
             const LdsAcc<LT> acc{base, B0, B1, B2, bx, by, bv};
             if (dep_j)
                 deposit_move(R, acc, g1, c1, g2, c2);
