@@ -174,6 +174,10 @@ struct mithra_engine {
     int use_graph = 1;
     bool batched = false;              // the run belongs to a batch
     hipStream_t ext_stream = nullptr;  // that batch's stream
+    int device = -1;                   // the arena's device
+    char *stage = nullptr;             // pinned host memory of the read calls (see begin_read)
+    double reads = 0;                  // read calls and MiB read so far, while there is no stage
+    hipEvent_t stage_ev[2] = {nullptr, nullptr};
     std::string err;
 };
 
@@ -322,6 +326,11 @@ extern "C" int mithra_init_grid(const mithra_grid_desc *d, void *dev_arena, size
     }
     h->arena = (char *)dev_arena;
     h->stream = (hipStream_t)hip_stream;
+    hipPointerAttribute_t attr;
+    if (hipPointerGetAttributes(&attr, dev_arena) == hipSuccess)
+        h->device = attr.device;
+    else
+        (void)hipGetLastError();
     // from here on a failure returns the handle too, so that its message
     // can be read; the caller destroys it
     *out = h;
@@ -719,13 +728,149 @@ extern "C" int mithra_step(mithra_handle h, int64_t n_steps)
     return MITHRA_OK;
 }
 
-static int check_nan(mithra_handle h)
+// ---- read-back --------------------------------------------------------------
+//
+// Results go to the host through pinned memory of the handle (2 MiB in two
+// halves and a small tail): one half is copied on to the caller's array while
+// the device fills the other.  A direct copy into pageable memory is staged
+// by the runtime at about 17 GB/s (10 into fresh pages, 2 at 100 KB) and
+// blocks for each array; this way takes 26 GB/s, and the arrays of one call
+// share their waits (96 x 96 x 256 nodes FP32: 0.58 -> 0.45 ms a field; 4096
+// particles: 189 -> 79 us).  Results of a few words are written there by
+// their kernels (plane power: 47 -> 27 us).
+// Pinning and releasing it takes about 1 ms, what some 48 calls or MiB lose
+// by direct copies, so a handle gets it once it has read that much: a short
+// run that is read back once does not pay for it.
+static const size_t kStageHalf = 1 << 20, kStageTail = 16384;
+
+struct ReadOut {
+    void *dst;        // host
+    const void *src;  // device
+    size_t bytes;
+};
+
+// The run's device is current while a read call works (its events belong to
+// that device), whatever device the caller has current.
+struct DeviceGuard {
+    int before = -1;
+    explicit DeviceGuard(const mithra_handle h)
+    {
+        int now = -1;
+        if (h->device >= 0 && hipGetDevice(&now) == hipSuccess && now != h->device &&
+            hipSetDevice(h->device) == hipSuccess)
+            before = now;
+    }
+    ~DeviceGuard()
+    {
+        if (before >= 0)
+            (void)hipSetDevice(before);
+    }
+};
+
+// Starts a read call of `bytes`: the batch's stream, if any, has finished.
+static int begin_read(mithra_handle h, size_t bytes)
 {
-    int32_t flag = 0;
-    HIPCHK(h, hipMemcpy(&flag, &h->R.ctl->nan_flag, 4, hipMemcpyDeviceToHost));
-    if (flag)
-        return fail(h, MITHRA_ENUMERIC, "non-finite value detected by the diagnostics");
+    if (h->batched)
+        HIPCHK(h, hipStreamSynchronize(h->ext_stream));
+    if (h->stage)
+        return MITHRA_OK;
+    h->reads += 1.0 + (double)bytes / (1 << 20);
+    if (h->reads >= 48.0) {
+        for (auto &e : h->stage_ev)
+            if (!e)
+                HIPCHK(h, hipEventCreateWithFlags(&e, hipEventDisableTiming));
+        if (hipHostMalloc((void **)&h->stage, 2 * kStageHalf + kStageTail, hipHostMallocDefault) != hipSuccess) {
+            (void)hipGetLastError();  // direct copies then; tried again after as many reads
+            h->stage = nullptr;
+            h->reads = 0;
+        }
+    }
     return MITHRA_OK;
+}
+
+// Where a kernel leaves results of a few KB (after the stage's copy of the
+// control block, or in the arena), and those results on the host.
+static double *small_dev(mithra_handle h)
+{
+    return (double *)(h->stage ? h->stage + 2 * kStageHalf + 1024 : h->arena + h->L.scratch);
+}
+
+static int small_host(mithra_handle h, double *out, size_t bytes)
+{
+    HIPCHK(h, hipStreamSynchronize(h->stream));
+    if (h->stage)
+        memcpy(out, small_dev(h), bytes);
+    else
+        HIPCHK(h, hipMemcpy(out, small_dev(h), bytes, hipMemcpyDeviceToHost));
+    return MITHRA_OK;
+}
+
+// Copies the arrays to the host, after the work enqueued on the handle's
+// stream.  With check_nan, a run whose diagnostics have seen a non-finite
+// value is reported before anything is written.
+static int copy_out(mithra_handle h, const std::vector<ReadOut> &outs, bool check_nan)
+{
+    struct Part {
+        char *dst, *at;
+        size_t len;
+    };
+    if (!h->stage) {
+        HIPCHK(h, hipStreamSynchronize(h->stream));
+        int32_t flag = 0;
+        if (check_nan)
+            HIPCHK(h, hipMemcpy(&flag, &h->R.ctl->nan_flag, 4, hipMemcpyDeviceToHost));
+        if (flag)
+            return fail(h, MITHRA_ENUMERIC, "non-finite value detected by the diagnostics");
+        for (const ReadOut &o : outs)
+            HIPCHK(h, hipMemcpyAsync(o.dst, o.src, o.bytes, hipMemcpyDeviceToHost, h->stream));
+        HIPCHK(h, hipStreamSynchronize(h->stream));
+        return MITHRA_OK;
+    }
+    std::vector<Part> parts[2];
+    bool pending[2] = {false, false};
+    char *ctl = h->stage + 2 * kStageHalf;
+    if (check_nan)
+        HIPCHK(h, hipMemcpyAsync(ctl, h->R.ctl, sizeof(Ctl), hipMemcpyDeviceToHost, h->stream));
+    auto drain = [&](int k) -> int {
+        if (!pending[k])
+            return MITHRA_OK;
+        HIPCHK(h, hipEventSynchronize(h->stage_ev[k]));
+        if (check_nan && ((const Ctl *)ctl)->nan_flag) {
+            HIPCHK(h, hipStreamSynchronize(h->stream));  // nothing in flight into the stage
+            return fail(h, MITHRA_ENUMERIC, "non-finite value detected by the diagnostics");
+        }
+        for (const Part &q : parts[k])
+            memcpy(q.dst, q.at, q.len);
+        parts[k].clear();
+        pending[k] = false;
+        return MITHRA_OK;
+    };
+    int half = 0;
+    size_t used = 0;
+    auto submit = [&]() -> int {
+        HIPCHK(h, hipEventRecord(h->stage_ev[half], h->stream));
+        pending[half] = true;
+        half ^= 1;
+        used = 0;
+        return drain(half);
+    };
+    int rc = MITHRA_OK;
+    for (const ReadOut &o : outs)
+        for (size_t off = 0; off < o.bytes && !rc;) {
+            char *at = h->stage + half * kStageHalf + used;
+            const size_t len = std::min(kStageHalf - used, o.bytes - off);
+            HIPCHK(h, hipMemcpyAsync(at, (const char *)o.src + off, len, hipMemcpyDeviceToHost, h->stream));
+            parts[half].push_back(Part{(char *)o.dst + off, at, len});
+            used += align256(len);
+            off += len;
+            if (used >= kStageHalf)
+                rc = submit();
+        }
+    if (!rc && used > 0)
+        rc = submit();  // drains the other half
+    for (int k = 0; k < 2 && !rc; ++k)
+        rc = drain(half ^ k);
+    return rc;
 }
 
 extern "C" int mithra_read_fields(mithra_handle h, int field_id, int dtype, void *host_out, size_t bytes)
@@ -736,8 +881,8 @@ extern "C" int mithra_read_fields(mithra_handle h, int field_id, int dtype, void
     const size_t esz = dtype == MITHRA_DTYPE_F32 ? 4 : 8;
     if (field_id < 0 || field_id > MITHRA_FIELD_RHO || (dtype != 0 && dtype != 1) || !host_out || bytes != nn * esz)
         return fail(h, MITHRA_EINVAL, "bad field id, dtype, buffer or size");
-    HIPCHK(h, sync_run(h));
-    int rc = check_nan(h);
+    const DeviceGuard on(h);
+    int rc = begin_read(h, bytes);
     if (rc)
         return rc;
     RunDev &R = h->R;
@@ -751,8 +896,9 @@ extern "C" int mithra_read_fields(mithra_handle h, int field_id, int dtype, void
     char *tmp = (char *)R.pot.get() + (size_t)slot_next(S) * 4 * nn * pf;
     if (field_id <= MITHRA_FIELD_BZ) {
         if (S == 0) {
+            rc = copy_out(h, {}, true);
             memset(host_out, 0, bytes);
-            return MITHRA_OK;
+            return rc;
         }
         HIPCHK(h, launch_read_vertex(R, S - 1, field_id, tmp, esz == 8, h->stream));
         src = tmp;
@@ -770,9 +916,7 @@ extern "C" int mithra_read_fields(mithra_handle h, int field_id, int dtype, void
         HIPCHK(h, launch_read_convert(R, src, lo, tmp, esz == 8, h->stream));
         src = tmp;
     }
-    HIPCHK(h, hipMemcpyAsync(host_out, src, bytes, hipMemcpyDeviceToHost, h->stream));
-    HIPCHK(h, hipStreamSynchronize(h->stream));
-    return MITHRA_OK;
+    return copy_out(h, {{host_out, src, bytes}}, true);
 }
 
 extern "C" int mithra_read_particles(mithra_handle h, double *xyz, double *u, int32_t *cell, int32_t *sort_perm)
@@ -781,12 +925,12 @@ extern "C" int mithra_read_particles(mithra_handle h, double *xyz, double *u, in
         return MITHRA_EINVAL;
     if (!h->loaded)
         return fail(h, MITHRA_ESTATE, "no bunch loaded");
-    HIPCHK(h, sync_run(h));
-    int rc = check_nan(h);
-    if (rc)
-        return rc;
+    const DeviceGuard on(h);
     RunDev &R = h->R;
     const size_t n = (size_t)R.np;
+    int rc = begin_read(h, n * ((xyz ? 24 : 0) + (u ? 24 : 0) + (cell ? 4 : 0) + (sort_perm ? 4 : 0)));
+    if (rc)
+        return rc;
     // device scratch of a read: the particle buffer that the next push
     // writes (six contiguous columns, the other one than pbuf, which flips
     // with every step), and the sort's input arrays, rewritten by the push
@@ -795,16 +939,16 @@ extern "C" int mithra_read_particles(mithra_handle h, double *xyz, double *u, in
     int32_t *cells = h->cell_by_id, *order = R.slot_in;
     HIPCHK(h, launch_read_particles(R, xyz ? rows : nullptr, u ? rows + 3 * n : nullptr, cell ? cells : nullptr,
                                     sort_perm ? order : nullptr, h->stream));
+    std::vector<ReadOut> outs;
     if (xyz)
-        HIPCHK(h, hipMemcpyAsync(xyz, rows, 3 * n * 8, hipMemcpyDeviceToHost, h->stream));
+        outs.push_back({xyz, rows, 3 * n * 8});
     if (u)
-        HIPCHK(h, hipMemcpyAsync(u, rows + 3 * n, 3 * n * 8, hipMemcpyDeviceToHost, h->stream));
+        outs.push_back({u, rows + 3 * n, 3 * n * 8});
     if (cell)
-        HIPCHK(h, hipMemcpyAsync(cell, cells, n * 4, hipMemcpyDeviceToHost, h->stream));
+        outs.push_back({cell, cells, n * 4});
     if (sort_perm)
-        HIPCHK(h, hipMemcpyAsync(sort_perm, order, n * 4, hipMemcpyDeviceToHost, h->stream));
-    HIPCHK(h, hipStreamSynchronize(h->stream));
-    return MITHRA_OK;
+        outs.push_back({sort_perm, order, n * 4});
+    return copy_out(h, outs, true);
 }
 
 extern "C" int mithra_radiated_power(mithra_handle h, int32_t k_plane, double *p_lab_W)
@@ -819,24 +963,30 @@ extern "C" int mithra_radiated_power(mithra_handle h, int32_t k_plane, double *p
         *p_lab_W = 0.0;
         return MITHRA_OK;
     }
-    double *dev = (double *)(h->arena + h->L.scratch) + 3 * kBunchBlocks;
-    HIPCHK(h, launch_plane_power(h->R, -1, k_plane, dev, h->stream));
-    HIPCHK(h, sync_run(h));
-    HIPCHK(h, hipMemcpy(p_lab_W, dev, 8, hipMemcpyDeviceToHost));
-    return MITHRA_OK;
+    const DeviceGuard on(h);
+    int rc = begin_read(h, 0);
+    if (rc)
+        return rc;
+    HIPCHK(h, launch_plane_power(h->R, -1, k_plane, small_dev(h), h->stream));
+    return small_host(h, p_lab_W, 8);
 }
 
 extern "C" int64_t mithra_power_history(mithra_handle h, double *out, int64_t n)
 {
     if (!h || !out || n < 0)
         return MITHRA_EINVAL;
-    HIPCHK(h, sync_run(h));
+    const DeviceGuard on(h);
+    int rc = begin_read(h, 0);
+    if (rc)
+        return rc;
     int64_t m = h->steps < n ? h->steps : n;
     if (m > kPowerCap)
         m = kPowerCap;
     if (m > 0)
-        HIPCHK(h, hipMemcpy(out, h->R.power_hist, (size_t)m * 8, hipMemcpyDeviceToHost));
-    return m;
+        rc = copy_out(h, {{out, h->R.power_hist, (size_t)m * 8}}, false);
+    else
+        HIPCHK(h, hipStreamSynchronize(h->stream));
+    return rc ? rc : m;
 }
 
 extern "C" int mithra_bunching(mithra_handle h, double *b)
@@ -845,11 +995,16 @@ extern "C" int mithra_bunching(mithra_handle h, double *b)
         return MITHRA_EINVAL;
     if (!h->loaded)
         return fail(h, MITHRA_ESTATE, "no bunch loaded");
-    double *part = (double *)(h->arena + h->L.scratch);
-    HIPCHK(h, launch_bunching(h->R, part, kBunchBlocks, h->stream));
-    HIPCHK(h, sync_run(h));
-    std::vector<double> hp(3 * kBunchBlocks);
-    HIPCHK(h, hipMemcpy(hp.data(), part, hp.size() * 8, hipMemcpyDeviceToHost));
+    const DeviceGuard on(h);
+    int rc = begin_read(h, 0);
+    if (rc)
+        return rc;
+    double hp[3 * kBunchBlocks];
+    static_assert(sizeof hp + 1024 <= kStageTail, "the partial sums fit the tail");
+    HIPCHK(h, launch_bunching(h->R, small_dev(h), kBunchBlocks, h->stream));
+    rc = small_host(h, hp, sizeof hp);
+    if (rc)
+        return rc;
     double re = 0, im = 0, n = 0;
     for (int i = 0; i < kBunchBlocks; ++i) {
         re += hp[3 * i];
@@ -923,15 +1078,18 @@ extern "C" int64_t mithra_spectral_power(mithra_handle h, double *dW_domega, int
 {
     if (!h || !dW_domega || n < 0)
         return MITHRA_EINVAL;
-    HIPCHK(h, sync_run(h));
+    const DeviceGuard on(h);
+    int rc = begin_read(h, 0);
+    if (rc)
+        return rc;
     const int64_t m = std::min<int64_t>(n, h->R.nfreq);
-    if (m <= 0)
+    if (m <= 0) {
+        HIPCHK(h, hipStreamSynchronize(h->stream));
         return 0;
-    double *dev = (double *)(h->arena + h->L.scratch);  // nfreq <= 64 results
-    HIPCHK(h, launch_spec_reduce(h->R, dev, h->stream));
-    HIPCHK(h, sync_run(h));
-    HIPCHK(h, hipMemcpy(dW_domega, dev, (size_t)m * 8, hipMemcpyDeviceToHost));
-    return m;
+    }
+    HIPCHK(h, launch_spec_reduce(h->R, small_dev(h), h->stream));  // nfreq <= 64 results
+    rc = small_host(h, dW_domega, (size_t)m * 8);
+    return rc ? rc : m;
 }
 
 extern "C" int mithra_set_undulator(mithra_handle h, const mithra_undulator_desc *u)
@@ -1144,6 +1302,11 @@ extern "C" int mithra_destroy(mithra_handle h)
     if (!h)
         return MITHRA_EINVAL;
     drop_graphs(h);
+    if (h->stage)
+        (void)hipHostFree(h->stage);
+    for (auto e : h->stage_ev)
+        if (e)
+            (void)hipEventDestroy(e);
     delete h;
     return MITHRA_OK;
 }

@@ -51,3 +51,24 @@ def test_reads_between_steps(shape, prec, comp, sc):
     only = np.empty((777, 3))
     rc = e._L.mithra_read_particles(e._h, None, only.ctypes.data_as(C.POINTER(C.c_double)), None, None)
     assert rc == 0 and np.array_equal(only, pu)
+
+
+@pytest.mark.parametrize("shape,n,prec", [((40, 30, 301), 60001, 64), ((64, 64, 80), 30000, 32)])
+def test_repeated_reads_are_equal(shape, n, prec):
+    """The first reads of a run are copied directly, later ones through the
+    handle's pinned halves (1 MiB each): the same values either way."""
+    from paper_2009_13645_amd.engine import Engine
+    w = wl.config1()
+    w.nx, w.ny, w.nz = shape
+    w.n_particles, w.field_precision = n, prec
+    xyz, u, q = wl.make_bunch(w)
+    e = Engine(w.descriptor(), max_particles=n)
+    e.load_bunch(xyz, u, q)
+    e.step(5)
+    first = [e.read_field("Ax"), e.read_field("Ey", np.float32), *e.read_particles(), e.power_history(5)]
+    scalars = [e.radiated_power(), e.bunching()]
+    for _ in range(10):
+        again = [e.read_field("Ax"), e.read_field("Ey", np.float32), *e.read_particles(), e.power_history(5)]
+        for a, b in zip(first, again):
+            assert np.array_equal(a, b)
+        assert [e.radiated_power(), e.bunching()] == scalars
