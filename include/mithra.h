@@ -329,8 +329,9 @@ int mithra_step_timed(mithra_handle h, int64_t n_steps, double *sweep_ms, double
 /* Measurement call: run n_steps exactly as mithra_step would, by direct
  * launches with HIP events on the handle's stream between the stages of
  * every step; synchronises, then adds the summed milliseconds per stage to
- * stage_ms[0..5] (0 field sweep, 1 Mur boundaries, 2 vertex E and B with
- * the plane-power partial sums, 3 gather + push + deposit, 4 box
+ * stage_ms[0..5] (0 field sweep, 1 nothing: the boundary faces are part of
+ * 2, 2 vertex E and B with the boundary faces, the plane-power partial sums
+ * and the plane spectrum, 3 gather + push + deposit, 4 box
  * reductions + bin and sort, 5 step tail) and of the whole steps to
  * stage_ms[6] (seven doubles, caller-owned).  Errors: EINVAL, ESTATE,
  * EDEVICE. */

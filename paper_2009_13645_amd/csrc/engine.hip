@@ -32,11 +32,9 @@ int sweep_shape_count();
 int sweep_default_shape(int nx, int ny, int nz, int precision);
 int sweep_effective_shape(const RunDev &R, int shape);
 hipError_t launch_mur(const RunDev &R, hipStream_t st);
-hipError_t launch_mur_faces(const RunDev &R, hipStream_t st);
 int sweep_fuses_xfaces(const RunDev &R, int shape);
-hipError_t launch_vertex_fields(const RunDev &R, int step_bias, int full, hipStream_t st);
+hipError_t launch_step_fields(const RunDev &R, hipStream_t st);
 hipError_t launch_plane_power(const RunDev &R, int step_bias, int kp, double *out, hipStream_t st, int end_step = 0);
-hipError_t launch_plane_spectrum(const RunDev &R, hipStream_t st);
 hipError_t launch_spec_reduce(const RunDev &R, double *out, hipStream_t st);
 hipError_t launch_seed_inject(const RunDev &R, hipStream_t st);
 hipError_t launch_gen_bunch(const RunDev &R, const GenParams &P, int pass, double *zrange, hipStream_t st);
@@ -65,7 +63,6 @@ hipError_t launch_vertex_group(const Group &g, int64_t total, int precision, hip
 int64_t power_blocks();
 hipError_t launch_power_group(const Group &g, int64_t total, const Group &gf, int64_t total_f, int precision,
                               hipStream_t st);
-hipError_t launch_vertex_power(const RunDev &R, hipStream_t st);
 hipError_t launch_push_group(const Group &g, int64_t total, int precision, int compensated, bool subs, hipStream_t st);
 hipError_t launch_box_group(const Group &g, int64_t total, hipStream_t st);
 hipError_t launch_sort_group(const Group &gs, int64_t total_s, const Group &gd, int64_t total_d, const Group &gp,
@@ -579,11 +576,6 @@ static int enqueue_sort_with_cells(mithra_handle h)
     return MITHRA_OK;
 }
 
-// One step on stream `st`: sweep, Mur, vertex fields (with the power's
-// partial sums), push + deposit, bin + sort, step tail.  With `ev` (seven
-// events), ev[i] is recorded before stage i and ev[6] after the last one:
-// stages 0 sweep, 1 Mur, 2 vertex fields, 3 push + deposit, 4 sort (with
-// the box reductions), 5 step tail (power sum, bookkeeping).
 static void drop_graphs(mithra_handle h)
 {
     for (auto &g : h->g1)
@@ -606,6 +598,12 @@ static bool step_sorts(const mithra_handle h, int64_t s)
     return h->R.sort_every <= 1 || (s + 1) % h->R.sort_every == 0 || sort_ends_step(h->R);
 }
 
+// One step on stream `st`: sweep, step fields (power's partial sums, plane
+// spectrum, boundary faces, vertex fields), push + deposit with the boundary's
+// edges, bin + sort, step tail.  With `ev` (seven events), ev[i] is recorded
+// before stage i and ev[6] after the last one: stages 0 sweep, 1 none (the
+// boundary faces are part of stage 2), 2 step fields, 3 push + deposit, 4 sort
+// (with the box reductions), 5 step tail (power sum, bookkeeping).
 static int enqueue_step_on(mithra_handle h, hipStream_t st, hipEvent_t *ev, int64_t s)
 {
     RunDev &R = h->R;
@@ -615,16 +613,10 @@ static int enqueue_step_on(mithra_handle h, hipStream_t st, hipEvent_t *ev, int6
     if (R.seed_on)  // before Mur: the boundary kernel reads the corrected planes
         HIPCHK(h, launch_seed_inject(R, st));
     HIPCHK(h, mark(1));
-    HIPCHK(h, launch_mur_faces(R, st));  // the push launch runs the edge workgroups
     HIPCHK(h, mark(2));
     // no mid-step bookkeeping: the box reductions after the push rewrite the
     // deposit box, the active-cell box and the active count whole
-    if (R.record_power)  // the power's partial sums ride on the vertex launch
-        HIPCHK(h, launch_vertex_power(R, st));
-    else
-        HIPCHK(h, launch_vertex_fields(R, 0, 0, st));
-    if (R.nfreq > 0)
-        HIPCHK(h, launch_plane_spectrum(R, st));
+    HIPCHK(h, launch_step_fields(R, st));
     HIPCHK(h, mark(3));
     // a small run's one-workgroup sort reduces the boxes and ends the step;
     // otherwise the box reduction after the push ends it (the power of the
@@ -1513,19 +1505,6 @@ extern "C" int mithra_autotune_sweep(mithra_handle h, int iters, int *best_shape
 // target step: its kernels return at once after that, so runs of different
 // lengths share the replays.
 
-// Workgroups of a member in a grouped vertex-field launch: an eighth of the
-// single run's count.  A member's particle box is a small part of its grid
-// (the grid holds the radiation around the bunch), and the workgroups past
-// the box find no node to do and return, but in a launch over many members
-// they fill the dispatch and the CU slots that the working ones wait for.
-// The grid-stride loop still covers a box as large as the grid (eight nodes
-// per thread then).
-static int64_t vertex_group_blocks(const RunDev &R)
-{
-    const int64_t b = vertex_blocks(R) / 8;
-    return b < 1 ? 1 : b;
-}
-
 struct GroupTab {
     Group g{};
     int64_t total = 0;
@@ -1658,7 +1637,7 @@ static int build_tables(mithra_batch b)
         if (!rc)
             rc = make_tab(b, mem, [](const RunDev &R) { return mur_edge_blocks(R); }, &b->mur_edge[pi]);
         if (!rc)
-            rc = make_tab(b, mem, [](const RunDev &R) { return vertex_group_blocks(R); }, &b->vertex[pi]);
+            rc = make_tab(b, mem, [](const RunDev &R) { return vertex_blocks(R); }, &b->vertex[pi]);
         if (!rc)
             rc = make_tab(b, memp, [](const RunDev &) { return power_blocks(); }, &b->power[pi]);
         if (!rc)

@@ -659,6 +659,14 @@ static __host__ __device__ inline int64_t clear_blocks_of(int ny, int nz)
     return r < 8 ? 8 : (r > 2048 ? 2048 : r);
 }
 
+// Face workgroups (per component) plus the source-clearing workgroups.
+__host__ __device__ inline int64_t mur_blocks_of(const RunDev &R)
+{
+    const int64_t nx = R.nx, ny = R.ny, nz = R.nz;
+    const int64_t nodes = 2 * (nx - 2) * (ny - 2) + 2 * (nx - 2) * (nz - 2) + (R.xface_fused ? 0 : 2 * (ny - 2) * (nz - 2));
+    return ((nodes + 255) / 256) * (R.space_charge ? 4 : 3) + clear_blocks_of(R.ny, R.nz);
+}
+
 // The n+1 value of face node c of axis ax from the levels n-1 (pm) and n
 // (p0), the new value npq of q, its neighbour inside, and the strides s1, s2
 // of the axes ax + 1 and ax + 2.
@@ -759,7 +767,22 @@ struct Mur {
 // K3: E and B at vertices
 // ---------------------------------------------------------------------------
 
-template <typename T>
+// The n+1 value of the boundary node beside interior node c0, one step of
+// `side` along axis AX, from its face update (not from memory).
+template <typename T, int AX>
+__device__ inline double face_beside(const RunDev &R, int64_t s, int comp, int side, int64_t c0)
+{
+    const int64_t st[3] = {1, R.nx, (int64_t)R.nx * R.ny};
+    return (double)mur_face(R, AX, pot_ptr<T>(R, slot_prev(s), comp), pot_ptr<T>(R, slot_cur(s), comp),
+                            (double)pot_ptr<T>(R, slot_next(s), comp)[c0], c0 + side * st[AX], c0, st[(AX + 1) % 3],
+                            st[(AX + 2) % 3]);
+}
+
+// E and B at interior node (i, j, k) from the levels n and n+1 of step s.
+// FACES: the boundary's n+1 values are not there yet (the boundary update
+// runs in the same launch), so a node beside the boundary computes the face
+// values it needs.
+template <typename T, bool FACES>
 __device__ inline void vertex_eb(const RunDev &R, int64_t s, int i, int j, int k, double E[3], double B[3])
 {
     const T *An[3], *Ap[3];
@@ -771,10 +794,37 @@ __device__ inline void vertex_eb(const RunDev &R, int64_t s, int i, int j, int k
     const int64_t sx = 1, sy = R.nx, sz = (int64_t)R.nx * R.ny;
     const double i2x = 0.5 / R.dx, i2y = 0.5 / R.dy, i2z = 0.5 / R.dz;
     auto dif = [&](const T *a, int64_t st) { return (double)a[c0 + st] - (double)a[c0 - st]; };
+    // differences of level n+1: A_z by y, A_y by z, A_x by z, A_z by x, A_y by x, A_x by y
+    double zy = dif(Ap[2], sy), yz = dif(Ap[1], sz), xz = dif(Ap[0], sz), zx = dif(Ap[2], sx), yx = dif(Ap[1], sx),
+           xy = dif(Ap[0], sy);
+    if constexpr (FACES) {
+        // the difference d of component c along an axis beside its face
+        auto fix = [&](double &d, int side, double face, const T *a, int64_t st) {
+            d = side < 0 ? (double)a[c0 + st] - face : face - (double)a[c0 - st];
+        };
+        if (j == 1 || j == R.ny - 2) {
+            const int side = j == 1 ? -1 : 1;
+            const double f2 = face_beside<T, 1>(R, s, 2, side, c0), f0 = face_beside<T, 1>(R, s, 0, side, c0);
+            fix(zy, side, f2, Ap[2], sy);
+            fix(xy, side, f0, Ap[0], sy);
+        }
+        if (k == 1 || k == R.nz - 2) {
+            const int side = k == 1 ? -1 : 1;
+            const double f1 = face_beside<T, 2>(R, s, 1, side, c0), f0 = face_beside<T, 2>(R, s, 0, side, c0);
+            fix(yz, side, f1, Ap[1], sz);
+            fix(xz, side, f0, Ap[0], sz);
+        }
+        if (!R.xface_fused && (i == 1 || i == R.nx - 2)) {
+            const int side = i == 1 ? -1 : 1;
+            const double f2 = face_beside<T, 0>(R, s, 2, side, c0), f1 = face_beside<T, 0>(R, s, 1, side, c0);
+            fix(zx, side, f2, Ap[2], sx);
+            fix(yx, side, f1, Ap[1], sx);
+        }
+    }
     // curl of A at n and at n+1, averaged
-    B[0] = 0.5 * ((dif(An[2], sy) + dif(Ap[2], sy)) * i2y - (dif(An[1], sz) + dif(Ap[1], sz)) * i2z);
-    B[1] = 0.5 * ((dif(An[0], sz) + dif(Ap[0], sz)) * i2z - (dif(An[2], sx) + dif(Ap[2], sx)) * i2x);
-    B[2] = 0.5 * ((dif(An[1], sx) + dif(Ap[1], sx)) * i2x - (dif(An[0], sy) + dif(Ap[0], sy)) * i2y);
+    B[0] = 0.5 * ((dif(An[2], sy) + zy) * i2y - (dif(An[1], sz) + yz) * i2z);
+    B[1] = 0.5 * ((dif(An[0], sz) + xz) * i2z - (dif(An[2], sx) + zx) * i2x);
+    B[2] = 0.5 * ((dif(An[1], sx) + yx) * i2x - (dif(An[0], sy) + xy) * i2y);
     double g[3] = {0.0, 0.0, 0.0};
     if (R.space_charge) {
         const T *ph = pot_ptr<T>(R, slot_cur(s), 3);
@@ -806,25 +856,19 @@ __device__ inline bool node_needed(const RunDev &R, int64_t s, int i, int j, int
     return false;
 }
 
-// E, B over the active-particle box of the last sort (full == 0) or over
-// all interior nodes (full == 1).  step_bias selects the step whose levels
-// are used (0 during a step, -1 after it for read-back).
-template <typename T>
+// E, B over the active-particle box of the last push, where a particle
+// gathers (FACES: see vertex_eb).
+template <typename T, bool FACES>
 struct VertexFields {
     static constexpr int kThreads = 256;
-    static __device__ void run(const RunDev &R, Blk blk, int step_bias, int full)
+    static __device__ void run(const RunDev &R, Blk blk)
     {
-        const int64_t s = R.ctl->step + step_bias;
+        const int64_t s = R.ctl->step;
         int lo[3], hi[3];
         const int n[3] = {R.nx, R.ny, R.nz};
         for (int a = 0; a < 3; ++a) {
-            if (full) {
-                lo[a] = 1;
-                hi[a] = n[a] - 2;
-            } else {
-                lo[a] = max(1, R.ctl->cell_lo[a]);
-                hi[a] = min(n[a] - 2, R.ctl->cell_hi[a] + 1);
-            }
+            lo[a] = max(1, R.ctl->cell_lo[a]);
+            hi[a] = min(n[a] - 2, R.ctl->cell_hi[a] + 1);
             if (hi[a] < lo[a])
                 return;
         }
@@ -847,10 +891,10 @@ struct VertexFields {
                 j = lo[1] + (int)((t / ex) % ey);
                 k = lo[2] + (int)(t / (ex * ey));
             }
-            if (!full && !node_needed(R, s, i, j, k))
+            if (!node_needed(R, s, i, j, k))
                 continue;  // no particle of this step gathers at this node
             double E[3], B[3];
-            vertex_eb<T>(R, s, i, j, k, E, B);
+            vertex_eb<T, FACES>(R, s, i, j, k, E, B);
             Vec<T, V> w[8 / V];
             const T all[8] = {(T)E[0], (T)E[1], (T)E[2], (T)B[0], (T)B[1], (T)B[2], (T)0, (T)0};
             for (int q = 0; q < 8; ++q)
@@ -869,7 +913,7 @@ struct VertexFields {
 // adds the partial sums needs a device-scope release fence in every block,
 // which writes back the XCD's L2: in a grouped launch of 32 runs that made
 // the stage six times slower.)
-template <typename T>
+template <typename T, bool FACES>
 struct PlanePower {
     static constexpr int kThreads = 256;
     static __device__ void run(const RunDev &R, Blk blk, int step_bias, int kp_arg)
@@ -883,7 +927,7 @@ struct PlanePower {
         for (int t = blk.id * 256 + threadIdx.x; t < wx * wy; t += kPowerBlocks * 256) {
             const int i = 1 + t % wx, j = 1 + t / wx;
             double E[3], B[3];
-            vertex_eb<T>(R, s, i, j, kp, E, B);
+            vertex_eb<T, FACES>(R, s, i, j, kp, E, B);
             const double Exl = g0 * (E[0] + b0 * kC * B[1]);
             const double Eyl = g0 * (E[1] - b0 * kC * B[0]);
             const double Bxl = g0 * (B[0] - b0 * E[1] / kC);
@@ -910,31 +954,21 @@ struct PlanePowerFinal {
     }
 };
 
-// Workgroups of the vertex-field launch (the same count on host and device).
+// Workgroups of the vertex fields (the same count on host and device): an
+// eighth of what one node per thread needs, 1024 at most.  The particle box
+// is a small part of the grid (the grid holds the radiation around the
+// bunch); workgroups past it find no node to do, but go through dispatch and
+// hold the slots that the working ones and the boundary's wait for.  The
+// grid-stride loop covers a box as large as the grid.  Single runs, the
+// launch that holds them (StepFields), with up to 8192 / 2048 / 1024
+// workgroups: 128 x 128 x 1024 nodes FP32 89 / 79 / 80 us, FP64 133 / 123 /
+// 122, 64 x 64 x 2800 FP64 143 / 133 / 131, 64 x 64 x 384 25 / 21 / 19.
 __host__ __device__ inline int64_t vertex_blocks_of(const RunDev &R)
 {
     const int64_t inner = (int64_t)(R.nx - 2) * (R.ny - 2) * (R.nz - 2);
-    const int64_t b = (inner + 255) / 256;
-    return b < 1 ? 1 : (b > 8192 ? 8192 : b);
+    const int64_t b = (inner + 255) / 256 / 8;
+    return b < 1 ? 1 : (b > 1024 ? 1024 : b);
 }
-
-// The step's vertex fields and the plane-power partial sums in one launch:
-// both read only the potentials of step s, which the push and the sort do
-// not change, so the partial sums equal those of a launch after the sort.
-// The power's workgroups come first, so that they do not form the launch's
-// tail.  Single-run steps only: in a grouped launch the merged body needs
-// 12-15 more VGPRs than the vertex fields alone, one wave per SIMD fewer.
-template <typename T>
-struct VertexPower {
-    static constexpr int kThreads = 256;
-    static __device__ void run(const RunDev &R, Blk blk)
-    {
-        if (blk.id < kPowerBlocks)
-            PlanePower<T>::run(R, Blk{blk.id, kPowerBlocks}, 0, -1);
-        else
-            VertexFields<T>::run(R, Blk{blk.id - kPowerBlocks, vertex_blocks_of(R)}, 0, 0);
-    }
-};
 
 // ---------------------------------------------------------------------------
 // Spectral radiated power: running Fourier transforms over the boosted time
@@ -949,7 +983,7 @@ __host__ __device__ inline double spec_nu(const RunDev &R, int f)
     return R.nfreq == 1 ? R.nu_min : R.nu_min + (R.nu_max - R.nu_min) * f / (double)(R.nfreq - 1);
 }
 
-template <typename T>
+template <typename T, bool FACES>
 struct PlaneSpectrum {
     static constexpr int kThreads = 256;
     static __device__ void run(const RunDev &R, Blk blk)
@@ -961,7 +995,7 @@ struct PlaneSpectrum {
             return;
         const int i = 1 + t % wx, j = 1 + t / wx;
         double E[3], B[3];
-        vertex_eb<T>(R, s, i, j, R.k_plane, E, B);
+        vertex_eb<T, FACES>(R, s, i, j, R.k_plane, E, B);
         const double g0 = R.gamma0, b0 = R.beta0;
         double F[4];
         F[0] = g0 * (E[0] + b0 * kC * B[1]);
@@ -980,6 +1014,43 @@ struct PlaneSpectrum {
                 acc[(2 * q + 1) * plane] += F[q] * sn;
             }
         }
+    }
+};
+
+__host__ __device__ inline int64_t spectrum_blocks_of(const RunDev &R)
+{
+    return R.nfreq > 0 ? ((int64_t)(R.nx - 2) * (R.ny - 2) + 255) / 256 : 0;
+}
+
+// A single run's stages between the sweep and the push in one launch: the
+// plane power's partial sums, the plane spectrum, the boundary faces with the
+// clearing of the next source set, and the vertex fields.  The power, the
+// spectrum and the vertex fields read the potentials of step s only, and
+// where they need the boundary's n+1 values they compute them (vertex_eb),
+// so nothing here waits for anything else here.  With the faces in a launch
+// before and the spectrum in one after: 64 x 64 x 256 FP64 with the spectrum
+// 92 -> 82 us a step, 32 x 32 x 64 FP64 39.9 -> 38.0, 64 x 64 x 2800 FP64 512
+// -> 494, 128 x 128 x 1024 FP32 430 -> 422 (entrance phase).
+// The short dependent chains come first, so that they do not form the
+// launch's tail, the boundary's plain streams last (before the vertex fields:
+// 80 -> 93 us at 128 x 128 x 1024 FP32).  Grouped steps keep the separate
+// launches: there the merged body needs more registers than the vertex fields
+// alone.
+template <typename T>
+struct StepFields {
+    static constexpr int kThreads = 256;
+    static __host__ __device__ int64_t power_blocks(const RunDev &R) { return R.record_power ? kPowerBlocks : 0; }
+    static __device__ void run(const RunDev &R, Blk blk)
+    {
+        const int64_t np = power_blocks(R), ns = spectrum_blocks_of(R), nm = mur_blocks_of(R);
+        if (blk.id < np)
+            PlanePower<T, true>::run(R, Blk{blk.id, kPowerBlocks}, 0, -1);
+        else if (blk.id < np + ns)
+            PlaneSpectrum<T, true>::run(R, Blk{blk.id - np, ns});
+        else if (blk.id < blk.n - nm)
+            VertexFields<T, true>::run(R, Blk{blk.id - np - ns, blk.n - np - ns - nm});
+        else
+            Mur<T>::run(R, Blk{blk.id - (blk.n - nm), nm});
     }
 };
 
@@ -1254,39 +1325,15 @@ static hipError_t launch_sweep_shape(const RunDev &R, int shape, hipStream_t st)
     }
 }
 
-// boundary nodes the Mur kernel updates (see Mur)
-// face nodes of the boundary (per component), and edge and corner nodes
-static int64_t mur_nodes(const RunDev &R)
-{
-    const int64_t nx = R.nx, ny = R.ny, nz = R.nz;
-    return 2 * (nx - 2) * (ny - 2) + 2 * (nx - 2) * (nz - 2) + (R.xface_fused ? 0 : 2 * (ny - 2) * (nz - 2));
-}
-
 hipError_t launch_sweep(const RunDev &R, int shape, hipStream_t st)
 {
     return R.precision == 32 ? launch_sweep_shape<float>(R, shape, st) : launch_sweep_shape<double>(R, shape, st);
 }
 
-// Mur face workgroups (per component) plus the source-clearing workgroups
-int64_t mur_blocks(const RunDev &R)
-{
-    return ((mur_nodes(R) + 255) / 256) * (R.space_charge ? 4 : 3) + clear_blocks_of(R.ny, R.nz);
-}
+int64_t mur_blocks(const RunDev &R) { return mur_blocks_of(R); }
 
 // Mur edge and corner workgroups (per component)
 int64_t mur_edge_blocks(const RunDev &R) { return mur_edge_blocks_of(R); }
-
-// The face workgroups (and the source clearing) only: the step's push
-// launch carries the edge workgroups.
-hipError_t launch_mur_faces(const RunDev &R, hipStream_t st)
-{
-    const unsigned blocks = (unsigned)mur_blocks(R);
-    if (R.precision == 32)
-        hipLaunchKernelGGL((k_run<Mur<float>>), dim3(blocks), dim3(256), 0, st, R);
-    else
-        hipLaunchKernelGGL((k_run<Mur<double>>), dim3(blocks), dim3(256), 0, st, R);
-    return hipGetLastError();
-}
 
 hipError_t launch_mur(const RunDev &R, hipStream_t st)
 {
@@ -1304,37 +1351,14 @@ hipError_t launch_mur(const RunDev &R, hipStream_t st)
 // workgroups of the vertex fields (a grid-stride loop over the box)
 int64_t vertex_blocks(const RunDev &R) { return vertex_blocks_of(R); }
 
-hipError_t launch_vertex_power(const RunDev &R, hipStream_t st)
+hipError_t launch_step_fields(const RunDev &R, hipStream_t st)
 {
-    const int64_t blocks = vertex_blocks_of(R) + kPowerBlocks;
+    const unsigned blocks = (unsigned)(StepFields<float>::power_blocks(R) + spectrum_blocks_of(R) + mur_blocks_of(R) +
+                                       vertex_blocks_of(R));
     if (R.precision == 32)
-        hipLaunchKernelGGL((k_run<VertexPower<float>>), dim3((unsigned)blocks), dim3(256), 0, st, R);
+        hipLaunchKernelGGL((k_run<StepFields<float>>), dim3(blocks), dim3(256), 0, st, R);
     else
-        hipLaunchKernelGGL((k_run<VertexPower<double>>), dim3((unsigned)blocks), dim3(256), 0, st, R);
-    return hipGetLastError();
-}
-
-hipError_t launch_vertex_fields(const RunDev &R, int step_bias, int full, hipStream_t st)
-{
-    const int64_t blocks = vertex_blocks(R);
-    if (R.precision == 32)
-        hipLaunchKernelGGL((k_run<VertexFields<float>, int, int>), dim3((unsigned)blocks), dim3(256), 0, st, R, step_bias,
-                           full);
-    else
-        hipLaunchKernelGGL((k_run<VertexFields<double>, int, int>), dim3((unsigned)blocks), dim3(256), 0, st, R, step_bias,
-                           full);
-    return hipGetLastError();
-}
-
-hipError_t launch_plane_spectrum(const RunDev &R, hipStream_t st)
-{
-    if (R.nfreq <= 0)
-        return hipSuccess;
-    const unsigned nb = (unsigned)(((int64_t)(R.nx - 2) * (R.ny - 2) + 255) / 256);
-    if (R.precision == 32)
-        hipLaunchKernelGGL((k_run<PlaneSpectrum<float>>), dim3(nb), dim3(256), 0, st, R);
-    else
-        hipLaunchKernelGGL((k_run<PlaneSpectrum<double>>), dim3(nb), dim3(256), 0, st, R);
+        hipLaunchKernelGGL((k_run<StepFields<double>>), dim3(blocks), dim3(256), 0, st, R);
     return hipGetLastError();
 }
 
@@ -1361,9 +1385,9 @@ hipError_t launch_seed_inject(const RunDev &R, hipStream_t st)
 hipError_t launch_plane_power(const RunDev &R, int step_bias, int kp, double *out, hipStream_t st, int end_step)
 {
     if (R.precision == 32)
-        hipLaunchKernelGGL((k_run<PlanePower<float>, int, int>), dim3(kPowerBlocks), dim3(256), 0, st, R, step_bias, kp);
+        hipLaunchKernelGGL((k_run<PlanePower<float, false>, int, int>), dim3(kPowerBlocks), dim3(256), 0, st, R, step_bias, kp);
     else
-        hipLaunchKernelGGL((k_run<PlanePower<double>, int, int>), dim3(kPowerBlocks), dim3(256), 0, st, R, step_bias, kp);
+        hipLaunchKernelGGL((k_run<PlanePower<double, false>, int, int>), dim3(kPowerBlocks), dim3(256), 0, st, R, step_bias, kp);
     hipLaunchKernelGGL((k_run<PlanePowerFinal, int, double *, int>), dim3(1), dim3(64), 0, st, R, step_bias, out, end_step);
     return hipGetLastError();
 }
@@ -1462,9 +1486,9 @@ hipError_t launch_vertex_group(const Group &g, int64_t total, int precision, hip
     if (total <= 0)
         return hipSuccess;
     if (precision == 32)
-        hipLaunchKernelGGL((k_group<VertexFields<float>, int, int>), dim3((unsigned)total), dim3(256), 0, st, g, 0, 0);
+        hipLaunchKernelGGL((k_group<VertexFields<float, false>>), dim3((unsigned)total), dim3(256), 0, st, g);
     else
-        hipLaunchKernelGGL((k_group<VertexFields<double>, int, int>), dim3((unsigned)total), dim3(256), 0, st, g, 0, 0);
+        hipLaunchKernelGGL((k_group<VertexFields<double, false>>), dim3((unsigned)total), dim3(256), 0, st, g);
     return hipGetLastError();
 }
 
@@ -1476,9 +1500,9 @@ hipError_t launch_power_group(const Group &g, int64_t total, const Group &gf, in
     if (total <= 0)
         return hipSuccess;
     if (precision == 32)
-        hipLaunchKernelGGL((k_group<PlanePower<float>, int, int>), dim3((unsigned)total), dim3(256), 0, st, g, 0, -1);
+        hipLaunchKernelGGL((k_group<PlanePower<float, false>, int, int>), dim3((unsigned)total), dim3(256), 0, st, g, 0, -1);
     else
-        hipLaunchKernelGGL((k_group<PlanePower<double>, int, int>), dim3((unsigned)total), dim3(256), 0, st, g, 0, -1);
+        hipLaunchKernelGGL((k_group<PlanePower<double, false>, int, int>), dim3((unsigned)total), dim3(256), 0, st, g, 0, -1);
     hipLaunchKernelGGL((k_group<PlanePowerFinal, int, double *, int>), dim3((unsigned)total_f), dim3(64), 0, st, gf, 0,
                        (double *)nullptr, 0);
     return hipGetLastError();

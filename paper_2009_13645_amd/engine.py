@@ -353,7 +353,9 @@ class Engine:
 
     def step_profile(self, n: int) -> dict:
         """n steps with HIP events between the stages of every step: summed
-        ms per stage (sweep, mur, vertex, push, sort, tail) and per step."""
+        ms per stage (sweep, mur, vertex, push, sort, tail) and per step.
+        The boundary faces and the plane spectrum are part of "vertex"
+        ("mur" is the cost of an empty stage)."""
         out = np.zeros(7)
         self._check(self._L.mithra_step_profile(self._h, int(n), _dp(out)))
         return dict(zip(self.STAGES, out.tolist()))
