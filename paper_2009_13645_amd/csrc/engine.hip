@@ -70,6 +70,8 @@ hipError_t launch_sort_group(const Group &gs, int64_t total_s, const Group &gd, 
 int64_t dep_blocks(int64_t np);
 int sort_passes(uint32_t key_inactive);
 int64_t sort_blocks(int64_t n);
+int sort_digit_width(int64_t n);
+size_t sort_hist_words(int64_t cap);
 
 // --- bookkeeping kernels (single thread) -----------------------------------
 
@@ -135,7 +137,7 @@ static Layout make_layout(const mithra_grid_desc *d, int64_t cap)
     L.cell_by_id = take(c * 4);
     L.sk = take(2 * c * 4);
     L.sv = take(2 * c * 4);
-    L.hist = take((256 * (size_t)sort_blocks((int64_t)c) + 256) * 4);
+    L.hist = take(sort_hist_words((int64_t)c) * 4);
     const size_t nparts = std::max((size_t)((c + 255) / 256), (size_t)kPartials);
     L.boxpart = take(8 * 4 * nparts);
     L.boxslot = take(16 * 4 * kBoxSlots);
@@ -554,6 +556,7 @@ static int finish_load(mithra_handle h, int64_t n, double q_macro)
 {
     RunDev &R = h->R;
     R.np = n;
+    R.digit_width = sort_digit_width(n);
     R.q = q_macro;
     R.qV = q_macro / (h->d.dx * h->d.dy * h->d.dz);
     for (int a = 0; a < 3; ++a)
@@ -1580,6 +1583,7 @@ static int make_tab(mithra_batch b, const std::vector<int> &mem, NB nb, GroupTab
     boff[0] = 0;
     for (size_t m = 0; m < n; ++m) {
         rd[m] = b->runs[mem[m]]->R;
+        rd[m].digit_width = 8;  // the grouped sort's
         nblk[m] = nb(rd[m]);
         boff[m + 1] = boff[m] + (nblk[m] + 7) / 8 * 8;
     }

@@ -365,16 +365,21 @@ __global__ __launch_bounds__(kSmallThreads) void k_sort_small(RunDev R, int step
     __shared__ uint32_t scan_tmp[4];
     const int n = (int)R.np;  // 1..kSmallChunk (checked by the launcher)
     const Ctl *ctl = R.ctl;
-    if (step_tail) {
-        BoxReduceStep::run(R, Blk{0, 1});
-        __syncthreads();  // the sort range is in the control block
-    }
-    const int npass = ctl->npass;
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    // the keys and the step's power (last wavefront: the partial sums are
+    // there since the step-fields launch) go on beside the box reductions
+    // (first wavefront)
     for (int i = t; i < n; i += kSmallThreads) {
         skey[0][i] = R.key_in[i];
         sval[0][i] = R.slot_in[i];
     }
+    if (step_tail) {
+        if (wave == kWaves - 1 && R.record_power)
+            plane_power_final(R, R.ctl->step, nullptr, 0);
+        BoxReduceStep::run(R, Blk{0, 1});
+        __syncthreads();  // the sort range is in the control block
+    }
+    const int npass = ctl->npass;
     const uint64_t lt = (lane == 0) ? 0ull : ((~0ull) >> (64 - lane));
     const int wbase = wave * (kSmallChunk / kWaves);
     for (int ps = 0; ps < npass; ++ps) {
@@ -450,14 +455,10 @@ __global__ __launch_bounds__(kSmallThreads) void k_sort_small(RunDev R, int step
     }
     if (step_tail) {
         __syncthreads();  // every read of the control block is done
-        if (t < 64) {
-            if (R.record_power)
-                plane_power_final(R, R.ctl->step, nullptr, 1);  // the first wavefront adds the partial sums
-            else if (t == 0) {
-                R.ctl->pbuf ^= 1;
-                R.ctl->nsort += 1;
-                R.ctl->step += 1;
-            }
+        if (t == 0) {
+            R.ctl->pbuf ^= 1;
+            R.ctl->nsort += 1;
+            R.ctl->step += 1;
         }
     }
 }
@@ -474,12 +475,12 @@ struct SortRange {
 // launches over runs of different sizes and key ranges: pass ps of a run
 // that needs fewer passes does nothing, and the gather reads the output of
 // the run's own last pass.
-__host__ __device__ inline int sort_passes_of(uint32_t key_inactive)
+__host__ __device__ inline int sort_passes_of(uint32_t key_inactive, int width)
 {
     int bits = 0;
     while (bits < 32 && (key_inactive >> bits) != 0)
         ++bits;
-    return bits <= 8 ? 1 : (bits + 7) / 8;
+    return bits <= width ? 1 : (bits + width - 1) / width;
 }
 
 struct RadixHistRun {
@@ -516,14 +517,207 @@ struct RadixScatterRun {
     }
 };
 
+// ---- wide digits, for runs of up to 2^18 particles -------------------------
+//
+// Bound by launches and by the latency of each kernel, not by bytes: all of
+// it fits the L2, and a pass is three launches of 4.5 us and more whatever it
+// does.  So the digits are up to 10 bits wide, the key range is split evenly
+// over the fewest passes (sort_range), and a workgroup takes 1024 elements, so
+// that small runs spread over more CUs.  Sort and box reductions of a push,
+// 8-bit digits before: 30001 particles in 45 x 51 x 97 nodes 35 -> 26 us (two
+// passes of 9 bits for three of 8), 131072 in 64 x 64 x 256 46 -> 32, 131072
+// in 64 x 64 x 2800 47 -> 44 (three passes), 262144 in 128 x 128 x 1024 48 ->
+// 47.  Digits of 11 and 12 bits save the third pass of wider ranges, but the
+// table of counts and the short digit runs cost more than the pass (131072 in
+// 128 x 128 x 1024: 50 and 53 against 43).  Larger runs keep the 8-bit digits:
+// there the runs are long and staged through LDS.
+constexpr int kWideBits = 10, kWideDigits = 1 << kWideBits;
+constexpr int kWideItems = 4, kWideChunk = kSortThreads * kWideItems;
+
+__device__ inline uint32_t wide_digit(const Ctl *ctl, uint32_t inactive, uint32_t key, int ps)
+{
+    const uint32_t x = key == inactive ? ctl->key_span : key - ctl->key_base;
+    return (x >> (ps * ctl->digit_bits)) & ((1u << ctl->digit_bits) - 1u);
+}
+
+// lanes of the wavefront whose digit equals this lane's
+__device__ inline uint64_t wide_peers(uint32_t d, bool ok, int bits)
+{
+    uint64_t peers = __ballot(ok);
+    for (int b = 0; b < bits; ++b) {
+        const uint64_t m = __ballot((d >> b) & 1);
+        peers &= ((d >> b) & 1) ? m : ~m;
+    }
+    return peers;
+}
+
+// per-workgroup digit histogram, digit-major: hist[d * nblocks + b]
+__global__ __launch_bounds__(kSortThreads) void k_wide_hist(RunDev R, int64_t nblocks, int ps)
+{
+    __shared__ uint32_t h[kWideDigits];
+    const Ctl *ctl = R.ctl;
+    if (ps >= ctl->npass)
+        return;
+    const uint32_t *keys = ps == 0 ? R.key_in : R.sk[(ps - 1) & 1];
+    const int nd = 1 << ctl->digit_bits;
+    const int64_t base = (int64_t)blockIdx.x * kWideChunk + threadIdx.x;
+    uint32_t k[kWideItems];
+    for (int it = 0; it < kWideItems; ++it)
+        k[it] = base + it * kSortThreads < R.np ? keys[base + it * kSortThreads] : 0u;
+    for (int d = threadIdx.x; d < nd; d += kSortThreads)
+        h[d] = 0;
+    __syncthreads();
+    for (int it = 0; it < kWideItems; ++it)
+        if (base + it * kSortThreads < R.np)
+            atomicAdd(&h[wide_digit(ctl, R.key_inactive, k[it], ps)], 1u);
+    __syncthreads();
+    for (int d = threadIdx.x; d < nd; d += kSortThreads)
+        R.hist[(int64_t)d * nblocks + blockIdx.x] = h[d];
+}
+
+// exclusive scan of each digit's row over the workgroups, and its total; one
+// wavefront per row at a time (at most 256 workgroups: four entries a lane)
+__global__ __launch_bounds__(kSortThreads) void k_wide_scan(RunDev R, int64_t nblocks, int ps)
+{
+    if (ps >= R.ctl->npass)
+        return;
+    uint32_t *tot = R.hist + (int64_t)kWideDigits * nblocks;
+    const int nd = 1 << R.ctl->digit_bits, lane = threadIdx.x & 63;
+    for (int d = blockIdx.x * (kSortThreads / 64) + (threadIdx.x >> 6); d < nd; d += gridDim.x * (kSortThreads / 64)) {
+        uint32_t *row = R.hist + (int64_t)d * nblocks;
+        uint32_t v[4], sum = 0;
+        for (int q = 0; q < 4; ++q) {
+            const int64_t e = 4 * (int64_t)lane + q;
+            v[q] = e < nblocks ? row[e] : 0u;
+            sum += v[q];
+        }
+        uint32_t inc = sum;
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t t = __shfl_up(inc, o);
+            if (lane >= o)
+                inc += t;
+        }
+        uint32_t run = inc - sum;
+        for (int q = 0; q < 4; ++q) {
+            const int64_t e = 4 * (int64_t)lane + q;
+            if (e < nblocks)
+                row[e] = run;
+            run += v[q];
+        }
+        if (lane == 63)
+            tot[d] = inc;
+    }
+}
+
+// stable scatter of one pass (ranks as in radix_scatter_blk: each wavefront a
+// contiguous quarter of the workgroup's elements, ballots, per-wavefront digit
+// counters)
+__global__ __launch_bounds__(kSortThreads) void k_wide_scatter(RunDev R, int64_t nblocks, int ps)
+{
+    constexpr int kWaves = kSortThreads / 64;
+    constexpr int kPer = kWideDigits / kSortThreads;  // digits a thread scans
+    __shared__ uint32_t start[kWaves][kWideDigits];   // per-wavefront counts, then output positions
+    __shared__ uint32_t scan_tmp[kWaves];
+    const Ctl *ctl = R.ctl;
+    if (ps >= ctl->npass)
+        return;
+    const uint32_t *keys_in = ps == 0 ? R.key_in : R.sk[(ps - 1) & 1];
+    const int32_t *vals_in = ps == 0 ? R.slot_in : R.sv[(ps - 1) & 1];
+    uint32_t *keys_out = R.sk[ps & 1];
+    int32_t *vals_out = R.sv[ps & 1];
+    const uint32_t *tot = R.hist + (int64_t)kWideDigits * nblocks;
+    const int bits = ctl->digit_bits, nd = 1 << bits;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t wbase = (int64_t)blockIdx.x * kWideChunk + (int64_t)wave * (kWideChunk / kWaves);
+    uint32_t k[kWideItems];
+    int32_t v[kWideItems];
+    for (int it = 0; it < kWideItems; ++it) {
+        const int64_t e = wbase + 64 * it + lane;
+        k[it] = e < R.np ? keys_in[e] : 0u;
+        v[it] = e < R.np ? vals_in[e] : 0;
+    }
+    // output position of the workgroup's first element of each of this
+    // thread's digits: the scan of the totals plus the workgroup's offset
+    const int per = nd > kSortThreads ? nd / kSortThreads : 1;
+    const int d0 = threadIdx.x * per;
+    uint32_t first[kPer], sum = 0;
+    for (int q = 0; q < kPer; ++q) {
+        const int d = d0 + q;
+        const bool ok = q < per && d < nd;
+        const uint32_t t = ok ? tot[d] : 0u;
+        first[q] = sum + (ok ? R.hist[(int64_t)d * nblocks + blockIdx.x] : 0u);
+        sum += t;
+    }
+    uint32_t inc = sum;
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t t = __shfl_up(inc, o);
+        if (lane >= o)
+            inc += t;
+    }
+    if (lane == 63)
+        scan_tmp[wave] = inc;
+    for (int d = threadIdx.x; d < nd; d += kSortThreads)
+        for (int w = 0; w < kWaves; ++w)
+            start[w][d] = 0;
+    __syncthreads();
+    uint32_t before_me = inc - sum;
+    for (int w = 0; w < wave; ++w)
+        before_me += scan_tmp[w];
+    const uint64_t lt = (lane == 0) ? 0ull : ((~0ull) >> (64 - lane));
+    uint32_t dig[kWideItems], rank[kWideItems];
+    for (int it = 0; it < kWideItems; ++it) {
+        const bool ok = wbase + 64 * it + lane < R.np;
+        const uint32_t d = ok ? wide_digit(ctl, R.key_inactive, k[it], ps) : 0u;
+        const uint64_t peers = wide_peers(d, ok, bits);
+        const uint32_t r = (uint32_t)__popcll(peers & lt);
+        const int leader = peers ? __builtin_ctzll(peers) : 0;
+        uint32_t b = 0;
+        if (ok && r == 0)
+            b = atomicAdd(&start[wave][d], (uint32_t)__popcll(peers));
+        dig[it] = d;
+        rank[it] = (uint32_t)__shfl((int)b, leader) + r;
+    }
+    __syncthreads();
+    for (int q = 0; q < kPer; ++q) {
+        const int d = d0 + q;
+        if (q < per && d < nd) {
+            uint32_t run = before_me + first[q];
+            for (int w = 0; w < kWaves; ++w) {
+                const uint32_t c = start[w][d];
+                start[w][d] = run;
+                run += c;
+            }
+        }
+    }
+    __syncthreads();
+    for (int it = 0; it < kWideItems; ++it)
+        if (wbase + 64 * it + lane < R.np) {
+            const uint32_t pos = start[wave][dig[it]] + rank[it];
+            keys_out[pos] = k[it];
+            vals_out[pos] = v[it];
+        }
+}
+
 // ---------------------------------------------------------------------------
 
 hipError_t launch_box_reduce(const RunDev &R, int64_t nblocks, const int32_t *part, int32_t *lo, int32_t *hi,
                              int32_t *count, hipStream_t st);
 
-int sort_passes(uint32_t key_inactive) { return sort_passes_of(key_inactive); }
+int sort_passes(uint32_t key_inactive) { return sort_passes_of(key_inactive, 8); }
 
 int64_t sort_blocks(int64_t n) { return (n + kSortChunk - 1) / kSortChunk; }
+
+// Digit width of a run of its own with n particles (grouped steps use 8),
+// and the histogram words a capacity of n needs (either width).
+int sort_digit_width(int64_t n) { return n > kSmallChunk && n <= (1 << 18) ? kWideBits : 8; }
+
+size_t sort_hist_words(int64_t cap)
+{
+    const size_t narrow = 256 * (size_t)sort_blocks(cap) + 256;
+    const int64_t c = cap < (1 << 18) ? cap : (1 << 18);
+    const size_t wide = (size_t)kWideDigits * ((c + kWideChunk - 1) / kWideChunk) + kWideDigits;
+    return narrow > wide ? narrow : wide;
+}
 
 // keys_ready: the push has already written the keys and the slots, and the
 // box reduction after it has set the active-cell box, the count and the
@@ -545,6 +739,14 @@ hipError_t launch_sort(const RunDev &R, hipStream_t st, bool keys_ready, int ste
     }
     if (R.np <= kSmallChunk) {
         hipLaunchKernelGGL(k_sort_small, dim3(1), dim3(kSmallThreads), 0, st, R, step_tail);
+    } else if (R.digit_width > 8) {
+        const int64_t nb = (R.np + kWideChunk - 1) / kWideChunk;
+        const int passes = sort_passes_of(R.key_inactive, R.digit_width);
+        for (int ps = 0; ps < passes; ++ps) {
+            hipLaunchKernelGGL(k_wide_hist, dim3((unsigned)nb), dim3(kSortThreads), 0, st, R, nb, ps);
+            hipLaunchKernelGGL(k_wide_scan, dim3(256), dim3(kSortThreads), 0, st, R, nb, ps);
+            hipLaunchKernelGGL(k_wide_scatter, dim3((unsigned)nb), dim3(kSortThreads), 0, st, R, nb, ps);
+        }
     } else {
         // as many passes as the widest key range needs; the ones the current
         // range does not need return at once

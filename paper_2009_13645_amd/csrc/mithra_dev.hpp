@@ -36,7 +36,8 @@ struct Ctl {
     int64_t target;        // step count at which a batched run stops (grouped launches only)
     uint32_t key_base;     // sort keys of the current sort are offset by this (active keys >= it)
     uint32_t key_span;     // active keys lie in [key_base, key_base + key_span); inactive sort as key_span
-    int32_t npass;         // radix passes the current sort needs (8-bit digits of key_span)
+    int32_t npass;         // radix passes the current sort needs (digits of key_span)
+    int32_t digit_bits;    // bits of a digit (8, or for wide digits an even split of the range)
     int32_t sorted_buf;    // sv[sorted_buf] holds the particles' slots in the order of the last sort;
                            // -1: no sort after the last push, the order is the buffer order
 };
@@ -137,6 +138,7 @@ struct RunDev {
     int tile[3];
     int ntile[3];
     uint32_t key_inactive;  // sort key of particles outside the active region
+    int digit_width;        // widest digit of the sort: 8, or 10 for a run of its own of up to 2^18 particles
     // storage (element type T = float or double for the field arrays)
     GlobalPtr<void> pot;        // [3 slots][4 comps][nn]
     GlobalPtr<void> src;        // [2 sets][4: Jx Jy Jz rho][nn]
@@ -463,10 +465,12 @@ __device__ inline void sort_range(const RunDev &R, bool may_skip)
     int bits = 0;
     while (bits < 32 && (span >> bits) != 0)
         ++bits;
-    const int np = bits <= 8 ? 1 : (bits + 7) / 8;
+    const int w = R.digit_width;
+    const int np = bits <= w ? 1 : (bits + w - 1) / w;
     c->key_base = base;
     c->key_span = span;
     c->npass = np;
+    c->digit_bits = w == 8 ? 8 : (bits <= np ? 1 : (bits + np - 1) / np);
     c->sorted_buf = (np - 1) & 1;
 }
 
