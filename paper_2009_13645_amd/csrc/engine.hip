@@ -27,7 +27,7 @@
 #include "mur_dev.hpp"
 
 namespace mithra {
-hipError_t launch_sweep(const RunDev &R, int shape, hipStream_t st);
+hipError_t launch_sweep(const RunDev &R, int shape, hipStream_t st, int tail = 0);
 int sweep_shape_count();
 int sweep_default_shape(int nx, int ny, int nz, int precision);
 int sweep_effective_shape(const RunDev &R, int shape);
@@ -607,12 +607,16 @@ static bool step_sorts(const mithra_handle h, int64_t s)
 // before stage i and ev[6] after the last one: stages 0 sweep, 1 none (the
 // boundary faces are part of stage 2), 2 step fields, 3 push + deposit, 4 sort
 // (with the box reductions), 5 step tail (power sum, bookkeeping).
-static int enqueue_step_on(mithra_handle h, hipStream_t st, hipEvent_t *ev, int64_t s)
+// tail: the sweep's launch ends the step before, which was enqueued with
+// `more`; more: another step follows in the same enqueueing, so this one may
+// leave its end to it (*left tells).
+static int enqueue_step_on(mithra_handle h, hipStream_t st, hipEvent_t *ev, int64_t s, bool tail = false,
+                           bool more = false, bool *left = nullptr)
 {
     RunDev &R = h->R;
     auto mark = [&](int i) { return ev ? hipEventRecord(ev[i], st) : hipSuccess; };
     HIPCHK(h, mark(0));
-    HIPCHK(h, launch_sweep(R, h->sweep_shape, st));
+    HIPCHK(h, launch_sweep(R, h->sweep_shape, st, tail ? 1 : 0));
     if (R.seed_on)  // before Mur: the boundary kernel reads the corrected planes
         HIPCHK(h, launch_seed_inject(R, st));
     HIPCHK(h, mark(1));
@@ -626,17 +630,19 @@ static int enqueue_step_on(mithra_handle h, hipStream_t st, hipEvent_t *ev, int6
     // step from the vertex launch's partial sums, then the bookkeeping), and
     // the sort passes, when the step sorts, follow
     const bool small = sort_ends_step(R);
-    HIPCHK(h, launch_push_deposit(R, st, !small, !small));
+    const bool leave = more && R.sort_every > 1 && (s + 1) % R.sort_every != 0 && sweep_fuses_xfaces(R, h->sweep_shape);
+    HIPCHK(h, launch_push_deposit(R, st, !small && !leave, !small));
     HIPCHK(h, mark(4));
-    if (step_sorts(h, s))
+    if (step_sorts(h, s) && !leave)
         HIPCHK(h, launch_sort(R, st, true, 1));
+    if (left)
+        *left = leave;
     HIPCHK(h, mark(5));
     HIPCHK(h, hipGetLastError());
     HIPCHK(h, mark(6));
     return MITHRA_OK;
 }
 
-static int enqueue_step(mithra_handle h, int64_t s) { return enqueue_step_on(h, h->stream, nullptr, s); }
 
 // Capture one step on a private stream (the caller's stream may be the
 // legacy default stream, which cannot be captured); the graph is then
@@ -655,8 +661,9 @@ static int build_graph(mithra_handle h, int nsteps, int64_t s0, hipGraphExec_t *
     int rc = MITHRA_OK;
     if (e == hipSuccess) {
         h->stream = cap;
+        bool left = false;  // the step before left its end to this one
         for (int i = 0; i < nsteps && rc == MITHRA_OK; ++i)
-            rc = enqueue_step(h, s0 + i);
+            rc = enqueue_step_on(h, cap, nullptr, s0 + i, left, i + 1 < nsteps, &left);
         h->stream = user;
         e = hipStreamEndCapture(cap, &g);
     }
@@ -714,7 +721,7 @@ extern "C" int mithra_step(mithra_handle h, int64_t n_steps)
             }
             HIPCHK(h, hipGraphLaunch(g, h->stream));
         } else {
-            int rc = enqueue_step(h, h->steps);
+            int rc = enqueue_step_on(h, h->stream, nullptr, h->steps);
             if (rc)
                 return rc;
         }

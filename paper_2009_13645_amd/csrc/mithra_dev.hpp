@@ -25,6 +25,8 @@ constexpr double kPi = 3.14159265358979323846;
 // step pipeline (and zeroed at init).
 struct Ctl {
     int64_t step;          // completed field steps
+    int64_t sweep_step;    // the step that the next sweep computes, set by the push before it: the
+                           // sweep's launch may carry the end of that push's step, which advances `step`
     int32_t pbuf;          // particle buffer holding the current sorted state
     int32_t nsort;         // sorts done
     int32_t dep_lo[2][3];  // node bounding box of the nonzero entries of source set s
@@ -544,14 +546,19 @@ struct BoxReduceStep {
 // bookkeeping (particle buffer, step counter).  For a single run whose sort,
 // when the step has one, runs as separate pass kernels: those read the sort
 // range and the slots, not the step counter or the buffer index, so the
-// step may end before them and no launch follows the sort.  Grouped steps
-// keep the separate end: there a member on its last step skips the stages
-// that come after its step counter has reached the target.
+// step may end before them and no launch follows the sort.  After a push that
+// no sort follows, one workgroup of the next step's sweep does it
+// (SweepWithTail) when that step is enqueued with this one; else it is a
+// launch.  Grouped steps keep the separate end: there a member on its last
+// step skips the stages that come after its step counter has reached the
+// target.
 struct BoxReduceEndStep {
     static constexpr int kThreads = 64;
     static __device__ void run(const RunDev &R, Blk blk)
     {
         BoxReduceStep::run(R, blk);
+        if (threadIdx.x >= 64)
+            return;  // in a larger workgroup (SweepWithTail) the first wavefront ends the step
         if (R.record_power) {
             plane_power_final(R, R.ctl->step, nullptr, 1);
         } else if (threadIdx.x == 0) {
