@@ -88,7 +88,7 @@ struct Sweep {
         if (comp >= 4)
             return;  // grid larger than the tiling (never for the launchers here)
 
-        const int64_t s = R.ctl->sweep_step;
+        const int64_t s = R.ctl->step;
         const int set_r = (int)(s & 1);
         const bool update = (comp < 3) || R.space_charge;
 
@@ -268,7 +268,11 @@ struct SweepVec {
         int2 sr[TZ][TY];
     };
 
-    static __device__ __attribute__((always_inline)) void run(const RunDev &R, Blk blk)
+    // OWN: a launch of a run of its own.  With tail it also carries the end of
+    // the step before (SweepWithTail): the step number is then next_step, and
+    // the deposit box, which that end writes, is not read.
+    template <bool OWN = false>
+    static __device__ __attribute__((always_inline)) void run(const RunDev &R, Blk blk, int tail = 0)
     {
         __shared__ Lds L;
         const int ntx = (R.nx + TW - 1) / TW;
@@ -285,21 +289,21 @@ struct SweepVec {
             return;  // grid larger than the tiling (never for the launchers here)
         if (comp == 3 && !R.space_charge)
             return;  // phi is not advanced without space charge (uniform per workgroup)
+        const int64_t s = OWN && tail ? R.ctl->next_step : R.ctl->step;
         // the component is a compile-time constant inside the body, so the
         // source loads of the other components do not exist there
         switch (comp) {
-        case 0: body<0>(R, L, tile_x, tile_y, chunk); break;
-        case 1: body<1>(R, L, tile_x, tile_y, chunk); break;
-        case 2: body<2>(R, L, tile_x, tile_y, chunk); break;
-        default: body<3>(R, L, tile_x, tile_y, chunk); break;
+        case 0: body<0, OWN>(R, L, tile_x, tile_y, chunk, s); break;
+        case 1: body<1, OWN>(R, L, tile_x, tile_y, chunk, s); break;
+        case 2: body<2, OWN>(R, L, tile_x, tile_y, chunk, s); break;
+        default: body<3, OWN>(R, L, tile_x, tile_y, chunk, s); break;
         }
     }
 
-    template <int COMP>
+    template <int COMP, bool OWN>
     static __device__ __attribute__((always_inline)) void body(const RunDev &R, Lds &L, int tile_x, int tile_y,
-                                                               int chunk)
+                                                               int chunk, int64_t s)
     {
-        const int64_t s = R.ctl->sweep_step;
         const int set_r = (int)(s & 1);
 
         const int lx = threadIdx.x % TXV, ly = threadIdx.x / TXV;
@@ -358,6 +362,12 @@ struct SweepVec {
             }
             __syncthreads();
         }
+        // grouped: a column outside the deposit box has no sources
+        bool src = work;
+        if constexpr (!OWN) {
+            const int *rlo = R.ctl->dep_lo[set_r], *rhi = R.ctl->dep_hi[set_r];
+            src = src && i0 + V - 1 >= rlo[0] && i0 <= rhi[0] + 1 && j >= rlo[1] && j <= rhi[1] + 1;
+        }
         const T *J = src_ptr<T>(R, set_r, COMP);
         const T *Jl = LO ? srclo_ptr<T>(R, set_r, COMP) : nullptr;
         const ST sfac = (ST)(COMP < 3 ? 0.5 * R.sfac_A : R.sfac_phi);
@@ -383,7 +393,7 @@ struct SweepVec {
             r.pm = vload_nt<T, V>(prev + c);
             // planes at or beyond ke are not stored: no source needed
             const int2 rg = L.sr[min(kk - kb, TZ - 1)][ly];
-            const bool in = work && kk < ke && i0 + V - 1 >= rg.x && i0 <= rg.y;
+            const bool in = src && kk < ke && i0 + V - 1 >= rg.x && i0 <= rg.y;
             const int64_t ca = in ? c : 0;
             r.a = vload<T, V>(J + ca);
             if constexpr (LO)
@@ -582,7 +592,7 @@ struct SweepVec {
 // (BoxReduceEndStep, in the first workgroup): a launch of 4.6 us less a step,
 // 72 x 56 x 136 nodes FP64 56 -> 53 us, 128 x 128 x 1024 FP32 373 -> 370.  Nothing that
 // the end of a step writes is read by the sweep: it takes its own step number
-// (sweep_step, set by the push) and the source rows, not the deposit box.
+// (next_step) and the source rows, not the deposit box.
 template <class S>
 struct SweepWithTail {
     static constexpr int kThreads = S::kThreads;
@@ -592,7 +602,7 @@ struct SweepWithTail {
             BoxReduceEndStep::run(R, Blk{0, 1});
             return;
         }
-        S::run(R, Blk{blk.id - tail, blk.n - tail});
+        S::template run<true>(R, Blk{blk.id - tail, blk.n - tail}, tail);
     }
 };
 
@@ -1057,6 +1067,8 @@ struct StepFields {
     static __device__ void run(const RunDev &R, Blk blk)
     {
         const int64_t np = power_blocks(R), ns = spectrum_blocks_of(R), nm = mur_blocks_of(R);
+        if (blk.id == 0 && threadIdx.x == 0)
+            R.ctl->next_step = R.ctl->step + 1;
         if (blk.id < np)
             PlanePower<T, true>::run(R, Blk{blk.id, kPowerBlocks}, 0, -1);
         else if (blk.id < np + ns)

@@ -45,8 +45,6 @@ struct PushDeposit {
         const int64_t s = R.ctl->step;
         const int pb = R.ctl->pbuf;
         const int set = MODE == 0 ? (int)((s + 1) & 1) : 0;
-        if (MODE == 0 && blk.id == 0 && threadIdx.x == 0)
-            R.ctl->sweep_step = s + 1;  // nothing in this launch reads it
         const int64_t p = (int64_t)blk.id * blockDim.x + threadIdx.x;
         double g1[3] = {0, 0, 0}, g2[3] = {0, 0, 0};
         int c1[3] = {0, 0, 0}, c2[3] = {0, 0, 0};

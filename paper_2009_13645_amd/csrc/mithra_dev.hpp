@@ -25,8 +25,6 @@ constexpr double kPi = 3.14159265358979323846;
 // step pipeline (and zeroed at init).
 struct Ctl {
     int64_t step;          // completed field steps
-    int64_t sweep_step;    // the step that the next sweep computes, set by the push before it: the
-                           // sweep's launch may carry the end of that push's step, which advances `step`
     int32_t pbuf;          // particle buffer holding the current sorted state
     int32_t nsort;         // sorts done
     int32_t dep_lo[2][3];  // node bounding box of the nonzero entries of source set s
@@ -42,6 +40,8 @@ struct Ctl {
     int32_t digit_bits;    // bits of a digit (8, or for wide digits an even split of the range)
     int32_t sorted_buf;    // sv[sorted_buf] holds the particles' slots in the order of the last sort;
                            // -1: no sort after the last push, the order is the buffer order
+    int64_t next_step;     // step + 1, set by StepFields: the step that a sweep computes whose launch
+                           // also ends the step before, and with that advances `step`
 };
 
 constexpr int kMaxBatch = 1;  // one run per RunDev
