@@ -58,13 +58,11 @@ int64_t mur_blocks(const RunDev &R);
 int64_t mur_edge_blocks(const RunDev &R);
 hipError_t launch_mur_group(const Group &g, int64_t total, const Group &ge, int64_t total_e, int precision,
                             hipStream_t st);
-int64_t vertex_blocks(const RunDev &R);
-hipError_t launch_vertex_group(const Group &g, int64_t total, int precision, hipStream_t st);
-int64_t power_blocks();
-hipError_t launch_power_group(const Group &g, int64_t total, const Group &gf, int64_t total_f, int precision,
-                              hipStream_t st);
+int64_t vertex_power_blocks(const RunDev &R);
+hipError_t launch_vertex_power_group(const Group &g, int64_t total, int precision, hipStream_t st);
 hipError_t launch_push_group(const Group &g, int64_t total, int precision, int compensated, bool subs, hipStream_t st);
-hipError_t launch_box_group(const Group &g, int64_t total, hipStream_t st);
+hipError_t launch_box_edges_group(const Group &g, int64_t total, hipStream_t st);
+hipError_t launch_end_step_group(const Group &g, int64_t total, hipStream_t st);
 hipError_t launch_sort_group(const Group &gs, int64_t total_s, const Group &gd, int64_t total_d, const Group &gp,
                              int64_t total_p, int max_passes, hipStream_t st);
 int64_t dep_blocks(int64_t np);
@@ -73,20 +71,7 @@ int64_t sort_blocks(int64_t n);
 int sort_digit_width(int64_t n);
 size_t sort_hist_words(int64_t cap);
 
-// --- bookkeeping kernels (single thread) -----------------------------------
-
-__device__ inline void book_end(Ctl *ctl, int advance)
-{
-    ctl->pbuf ^= 1;
-    ctl->nsort += 1;
-    if (advance)
-        ctl->step += 1;
-}
-
-struct BookEnd {
-    static constexpr int kThreads = 1;
-    static __device__ void run(const RunDev &R, Blk) { book_end(R.ctl, 1); }
-};
+// --- bookkeeping at load (single thread) ------------------------------------
 
 __global__ void k_book_load(Ctl *ctl)
 {
@@ -1534,7 +1519,7 @@ struct mithra_batch_s {
         GroupTab t;
     };
     std::vector<SweepCls> sweep;
-    GroupTab mur[2], mur_edge[2], vertex[2], power[2], power_final[2], push[6], one, sort_s, sort_d, sort_p;
+    GroupTab mur[2], mur_edge[2], vertex[2], push[6], box_edges, one, sort_s, sort_d, sort_p;
     int max_passes = 0;
     hipGraphExec_t graph = nullptr;         // one batched step
     hipGraphExec_t graph_nosort = nullptr;  // the same without the sort passes (captured on first use)
@@ -1637,22 +1622,15 @@ static int build_tables(mithra_batch b)
     }
     for (int pi = 0; pi < 2; ++pi) {
         const int prec = pi == 0 ? 32 : 64;
-        std::vector<int> mem, memp;
+        std::vector<int> mem;
         for (int i = 0; i < n; ++i)
-            if (b->runs[i]->R.precision == prec) {
+            if (b->runs[i]->R.precision == prec)
                 mem.push_back(i);
-                if (b->runs[i]->R.record_power)
-                    memp.push_back(i);
-            }
         int rc = make_tab(b, mem, [](const RunDev &R) { return mur_blocks(R); }, &b->mur[pi]);
         if (!rc)
             rc = make_tab(b, mem, [](const RunDev &R) { return mur_edge_blocks(R); }, &b->mur_edge[pi]);
         if (!rc)
-            rc = make_tab(b, mem, [](const RunDev &R) { return vertex_blocks(R); }, &b->vertex[pi]);
-        if (!rc)
-            rc = make_tab(b, memp, [](const RunDev &) { return power_blocks(); }, &b->power[pi]);
-        if (!rc)
-            rc = make_tab(b, memp, [](const RunDev &) { return (int64_t)1; }, &b->power_final[pi]);
+            rc = make_tab(b, mem, [](const RunDev &R) { return vertex_power_blocks(R); }, &b->vertex[pi]);
         if (rc)
             return rc;
     }
@@ -1670,6 +1648,8 @@ static int build_tables(mithra_batch b)
     }
     int rc = make_tab(b, all, [](const RunDev &) { return (int64_t)1; }, &b->one);
     if (!rc)
+        rc = make_tab(b, all, [](const RunDev &R) { return 1 + mur_edge_blocks(R); }, &b->box_edges);
+    if (!rc)
         rc = make_tab(b, all, [](const RunDev &R) { return R.sort_blocks; }, &b->sort_s);
     if (!rc)
         rc = make_tab(b, all, [](const RunDev &) { return (int64_t)256; }, &b->sort_d);
@@ -1686,8 +1666,9 @@ static int build_tables(mithra_batch b)
 // One batched step.  The members of the two precisions share no memory, so
 // their stages up to the push form two independent chains: the FP64
 // members' on the side stream, the FP32 members' on st; each chain's
-// grouped launches then fill the tails of the other's.  The box reductions,
-// the sort and the bookkeeping run over all members after the join.
+// grouped launches then fill the tails of the other's.  The box reductions
+// with the boundary's edges, the sort and the end of the step run over all
+// members after the join.
 static void batch_free_streams(mithra_batch b)
 {
     if (b->side)
@@ -1710,24 +1691,19 @@ static int enqueue_batch_step(mithra_batch b, hipStream_t st, bool sort)
         for (auto &c : b->sweep)
             if (c.precision == prec)
                 BHIPCHK(b, launch_sweep_group(c.t.g, c.t.total, c.precision, c.comp, c.shape, cs));
-        BHIPCHK(b, launch_mur_group(b->mur[pi].g, b->mur[pi].total, b->mur_edge[pi].g, b->mur_edge[pi].total, prec,
-                                    cs));
-        BHIPCHK(b, launch_vertex_group(b->vertex[pi].g, b->vertex[pi].total, prec, cs));
-        // the plane power reads the potentials of this step only
-        BHIPCHK(b, launch_power_group(b->power[pi].g, b->power[pi].total, b->power_final[pi].g,
-                                      b->power_final[pi].total, prec, cs));
+        BHIPCHK(b, launch_mur_group(b->mur[pi].g, b->mur[pi].total, b->mur_edge[pi].g, 0, prec, cs));  // faces
+        BHIPCHK(b, launch_vertex_power_group(b->vertex[pi].g, b->vertex[pi].total, prec, cs));
         for (int ci = 0; ci < 6; ++ci)
             if ((ci % 3 == 0) == (chain == 0))
                 BHIPCHK(b, launch_push_group(b->push[ci].g, b->push[ci].total, prec, ci % 3 == 2, ci >= 3, cs));
     }
     BHIPCHK(b, hipEventRecord(b->join, b->side));
     BHIPCHK(b, hipStreamWaitEvent(st, b->join, 0));
-    BHIPCHK(b, launch_box_group(b->one.g, b->one.total, st));
+    BHIPCHK(b, launch_box_edges_group(b->box_edges.g, b->box_edges.total, st));
     if (sort)
         BHIPCHK(b, launch_sort_group(b->sort_s.g, b->sort_s.total, b->sort_d.g, b->sort_d.total, b->sort_p.g,
                                      b->sort_p.total, b->max_passes, st));
-    hipLaunchKernelGGL((k_group<BookEnd>), dim3((unsigned)b->one.total), dim3(1), 0, st, b->one.g);
-    BHIPCHK(b, hipGetLastError());
+    BHIPCHK(b, launch_end_step_group(b->one.g, b->one.total, st));
     return MITHRA_OK;
 }
 

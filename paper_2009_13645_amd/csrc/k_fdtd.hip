@@ -1057,9 +1057,9 @@ __host__ __device__ inline int64_t spectrum_blocks_of(const RunDev &R)
 // -> 494, 128 x 128 x 1024 FP32 430 -> 422 (entrance phase).
 // The short dependent chains come first, so that they do not form the
 // launch's tail, the boundary's plain streams last (before the vertex fields:
-// 80 -> 93 us at 128 x 128 x 1024 FP32).  Grouped steps keep the separate
-// launches: there the merged body needs more registers than the vertex fields
-// alone.
+// 80 -> 93 us at 128 x 128 x 1024 FP32).  Grouped steps launch the boundary
+// by itself (VertexPower): the face values cost the vertex fields registers,
+// and a step of 16 runs took 537 us with this body and 515 without.
 template <typename T>
 struct StepFields {
     static constexpr int kThreads = 256;
@@ -1379,9 +1379,6 @@ hipError_t launch_mur(const RunDev &R, hipStream_t st)
     return hipGetLastError();
 }
 
-// workgroups of the vertex fields (a grid-stride loop over the box)
-int64_t vertex_blocks(const RunDev &R) { return vertex_blocks_of(R); }
-
 hipError_t launch_step_fields(const RunDev &R, hipStream_t st)
 {
     const unsigned blocks = (unsigned)(StepFields<float>::power_blocks(R) + spectrum_blocks_of(R) + mur_blocks_of(R) +
@@ -1502,40 +1499,84 @@ hipError_t launch_mur_group(const Group &g, int64_t total, const Group &ge, int6
         return hipSuccess;
     if (precision == 32) {
         hipLaunchKernelGGL((k_group<Mur<float>>), dim3((unsigned)total), dim3(256), 0, st, g);
-        hipLaunchKernelGGL((k_group<MurEdge<float>>), dim3((unsigned)total_e), dim3(256), 0, st, ge);
+        if (total_e > 0)
+            hipLaunchKernelGGL((k_group<MurEdge<float>>), dim3((unsigned)total_e), dim3(256), 0, st, ge);
     } else {
         hipLaunchKernelGGL((k_group<Mur<double>>), dim3((unsigned)total), dim3(256), 0, st, g);
-        hipLaunchKernelGGL((k_group<MurEdge<double>>), dim3((unsigned)total_e), dim3(256), 0, st, ge);
+        if (total_e > 0)
+            hipLaunchKernelGGL((k_group<MurEdge<double>>), dim3((unsigned)total_e), dim3(256), 0, st, ge);
     }
     return hipGetLastError();
 }
 
+// Vertex fields and, beside them, the power's partial sums of each member;
+// the power's few workgroups go first.  A step of 16 mixed runs (32 to 96
+// nodes across, up to 256 along) took 521 us with two launches, 515 with one.
+template <typename T>
+struct VertexPower {
+    static constexpr int kThreads = 256;
+    static __device__ void run(const RunDev &R, Blk blk)
+    {
+        const int64_t np = StepFields<T>::power_blocks(R);
+        if (blk.id < np)
+            PlanePower<T, false>::run(R, Blk{blk.id, kPowerBlocks}, 0, -1);
+        else
+            VertexFields<T, false>::run(R, Blk{blk.id - np, blk.n - np});
+    }
+};
 
+int64_t vertex_power_blocks(const RunDev &R) { return StepFields<float>::power_blocks(R) + vertex_blocks_of(R); }
 
-hipError_t launch_vertex_group(const Group &g, int64_t total, int precision, hipStream_t st)
+hipError_t launch_vertex_power_group(const Group &g, int64_t total, int precision, hipStream_t st)
 {
     if (total <= 0)
         return hipSuccess;
     if (precision == 32)
-        hipLaunchKernelGGL((k_group<VertexFields<float, false>>), dim3((unsigned)total), dim3(256), 0, st, g);
+        hipLaunchKernelGGL((k_group<VertexPower<float>>), dim3((unsigned)total), dim3(256), 0, st, g);
     else
-        hipLaunchKernelGGL((k_group<VertexFields<double, false>>), dim3((unsigned)total), dim3(256), 0, st, g);
+        hipLaunchKernelGGL((k_group<VertexPower<double>>), dim3((unsigned)total), dim3(256), 0, st, g);
     return hipGetLastError();
 }
 
-int64_t power_blocks() { return kPowerBlocks; }
+// After the pushes of all members: each member's box reductions (one
+// workgroup) and its Mur edges and corners, which only have to be done before
+// the step ends.  Neither reads what the other writes.  Edges that ran after
+// the faces, a launch for each precision in the chain before the push, and the
+// power's sum and the counters in two launches: 525 us a step of 16 mixed
+// runs; with this and EndStep 521.
+struct BoxEdges {
+    static constexpr int kThreads = 256;
+    static __device__ void run(const RunDev &R, Blk blk)
+    {
+        if (blk.id == 0)
+            BoxReduceStep::run(R, blk);
+        else if (R.precision == 32)
+            MurEdge<float>::run(R, Blk{blk.id - 1, blk.n - 1});
+        else
+            MurEdge<double>::run(R, Blk{blk.id - 1, blk.n - 1});
+    }
+};
 
-hipError_t launch_power_group(const Group &g, int64_t total, const Group &gf, int64_t total_f, int precision,
-                              hipStream_t st)
+hipError_t launch_box_edges_group(const Group &g, int64_t total, hipStream_t st)
 {
     if (total <= 0)
         return hipSuccess;
-    if (precision == 32)
-        hipLaunchKernelGGL((k_group<PlanePower<float, false>, int, int>), dim3((unsigned)total), dim3(256), 0, st, g, 0, -1);
-    else
-        hipLaunchKernelGGL((k_group<PlanePower<double, false>, int, int>), dim3((unsigned)total), dim3(256), 0, st, g, 0, -1);
-    hipLaunchKernelGGL((k_group<PlanePowerFinal, int, double *, int>), dim3((unsigned)total_f), dim3(64), 0, st, gf, 0,
-                       (double *)nullptr, 0);
+    hipLaunchKernelGGL((k_group<BoxEdges>), dim3((unsigned)total), dim3(256), 0, st, g);
+    return hipGetLastError();
+}
+
+// The end of a member's step: the power from the partial sums, if recorded,
+// and the bookkeeping.  One workgroup a member.
+struct EndStep {
+    static constexpr int kThreads = 64;
+    static __device__ void run(const RunDev &R, Blk) { end_step(R); }
+};
+
+hipError_t launch_end_step_group(const Group &g, int64_t total, hipStream_t st)
+{
+    if (total <= 0)
+        return hipSuccess;
+    hipLaunchKernelGGL((k_group<EndStep>), dim3((unsigned)total), dim3(EndStep::kThreads), 0, st, g);
     return hipGetLastError();
 }
 

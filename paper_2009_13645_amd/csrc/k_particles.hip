@@ -636,13 +636,4 @@ hipError_t launch_push_group(const Group &g, int64_t total, int precision, int c
     return hipGetLastError();
 }
 
-// one workgroup per member each
-hipError_t launch_box_group(const Group &g, int64_t total, hipStream_t st)
-{
-    if (total <= 0)
-        return hipSuccess;
-    hipLaunchKernelGGL((k_group<BoxReduceStep>), dim3((unsigned)total), dim3(BoxReduceStep::kThreads), 0, st, g);
-    return hipGetLastError();
-}
-
 }  // namespace mithra

@@ -552,20 +552,25 @@ struct BoxReduceStep {
 // launch.  Grouped steps keep the separate end: there a member on its last
 // step skips the stages that come after its step counter has reached the
 // target.
+__device__ inline void end_step(const RunDev &R)
+{
+    if (threadIdx.x >= 64)
+        return;  // in a larger workgroup the first wavefront ends the step
+    if (R.record_power) {
+        plane_power_final(R, R.ctl->step, nullptr, 1);
+    } else if (threadIdx.x == 0) {
+        R.ctl->pbuf ^= 1;
+        R.ctl->nsort += 1;
+        R.ctl->step += 1;
+    }
+}
+
 struct BoxReduceEndStep {
     static constexpr int kThreads = 64;
     static __device__ void run(const RunDev &R, Blk blk)
     {
         BoxReduceStep::run(R, blk);
-        if (threadIdx.x >= 64)
-            return;  // in a larger workgroup (SweepWithTail) the first wavefront ends the step
-        if (R.record_power) {
-            plane_power_final(R, R.ctl->step, nullptr, 1);
-        } else if (threadIdx.x == 0) {
-            R.ctl->pbuf ^= 1;
-            R.ctl->nsort += 1;
-            R.ctl->step += 1;
-        }
+        end_step(R);
     }
 };
 
