@@ -619,10 +619,76 @@ __device__ inline uint32_t face_div(int64_t r, int64_t half, int d)
     return (uint32_t)(r / d);
 }
 
-// The source set that this step's deposit accumulates into is zeroed on the
-// node box of its previous deposit, every component.  The set was last read
-// by the previous step's sweep, and the deposit runs after this kernel.
-// One wavefront per x-row of the box; row indices are wavefront-uniform.
+// Is node (i, j, k) a corner of an active cell whose sort tile is marked with
+// a step of s - back .. s?  The push of step s-1 (or the load) marks the tiles
+// of the cells its particles end in with s; a node's cells are i-1..i on each
+// axis, within the active range 1..n-3.  The eight marks load without a branch
+// between them.
+__device__ inline bool node_marked(const RunDev &R, int64_t s, uint32_t back, int i, int j, int k)
+{
+    const uint32_t now = (uint32_t)s;
+    uint32_t x[2], y[2], z[2];
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+        x[a] = fdiv((uint32_t)min(max(i - 1 + a, 1), R.nx - 3), R.tdiv[0]);
+        y[a] = fdiv((uint32_t)min(max(j - 1 + a, 1), R.ny - 3), R.tdiv[1]);
+        z[a] = fdiv((uint32_t)min(max(k - 1 + a, 1), R.nz - 3), R.tdiv[2]);
+    }
+    bool any = false;
+#pragma unroll
+    for (int a = 0; a < 8; ++a)
+        any |= now - R.tile_flag[((int64_t)z[a >> 2] * R.ntile[1] + y[(a >> 1) & 1]) * R.ntile[0] + x[a & 1]] <= back;
+    return any;
+}
+
+// Node t of a box, x fastest; by multiply-high when that is exact
+// (t * max(ex, ey) < 2^32).
+struct BoxNodes {
+    int l0, l1, l2;
+    int64_t ex, ey, tot;
+    FastDiv fx, fy;
+    bool fast;
+    __device__ BoxNodes(int l0, int l1, int l2, int64_t ex, int64_t ey, int64_t ez)
+        : l0(l0), l1(l1), l2(l2), ex(ex), ey(ey), tot(ex * ey * ez), fx(fast_div((uint32_t)ex)),
+          fy(fast_div((uint32_t)ey)), fast((uint64_t)tot * (uint64_t)(ex > ey ? ex : ey) < (1ull << 32))
+    {
+    }
+    __device__ void node(int64_t t, int &i, int &j, int &k) const
+    {
+        if (fast) {
+            const uint32_t t32 = (uint32_t)t, row = fdiv(t32, fx);
+            const uint32_t kk = fdiv(row, fy);
+            i = l0 + (int)(t32 - row * (uint32_t)ex);
+            j = l1 + (int)(row - kk * (uint32_t)ey);
+            k = l2 + (int)kk;
+        } else {
+            i = l0 + (int)(t % ex);
+            j = l1 + (int)((t / ex) % ey);
+            k = l2 + (int)(t / (ex * ey));
+        }
+    }
+};
+
+// The source set that this step's deposit accumulates into is zeroed where
+// its previous deposit, by the push of step s-2, may lie.  The set was last
+// read by the previous step's sweep, and the deposit runs after this kernel.
+// A deposit lies at the corners of the active cells in which that push began
+// and ended a particle's move, within the set's node box.  The tiles of those
+// cells carry a mark of s-2 (where moves began; set before that push), s-1
+// (where they ended) or, renewed since, s.  Tiles never marked hold -1, so at
+// step 1, whose set the load deposits into without marking where its moves
+// begin, every node of the box counts.
+// Bound by its writes, which also push the sweep's planes out of the last-level
+// cache: of the 4.0 million nodes in example 1's box (64 x 64 x 2800 FP64) the
+// marked tiles hold a third, and zeroing the whole box (rows of it, one
+// wavefront each) took 485 us a step, this 454 (the sweep 200 -> 179, this
+// launch 131 -> 123); 128 x 128 x 1024 FP32 367 -> 357.
+// Boxes of few bytes are zeroed whole: there the caches take the writes, and
+// looking up the marks costs more (5 MB at 64 x 64 x 384 FP32: 84.5 us a step
+// zeroed whole, 85.9 by marks; 16 to 30 MB at 128 x 128 x 1024 FP32: 357.4
+// against 354.7 by marks).
+constexpr int64_t kZeroAll = 8 << 20;
+
 template <typename T>
 __device__ inline void clear_next_sources(const RunDev &R, int64_t b, int64_t nb)
 {
@@ -634,44 +700,40 @@ __device__ inline void clear_next_sources(const RunDev &R, int64_t b, int64_t nb
     const int ex = hi[0] - l0 + 1, ey = hi[1] - l1 + 1, ez = hi[2] - l2 + 1;
     if (ex <= 0 || ey <= 0 || ez <= 0)
         return;
+    const int64_t first = b * blockDim.x + threadIdx.x, step = nb * blockDim.x;
     // the set's source row ranges, on the rows the deposit's boxes may have
     // grown them to (one more node along y and z)
     {
         int32_t *slo = R.srow_lo + (size_t)set_c * R.nz * R.ny;
         int32_t *shi = R.srow_hi + (size_t)set_c * R.nz * R.ny;
         const int ry = ey + 1, nr = ry * (ez + 1);
-        for (int64_t r = b * blockDim.x + threadIdx.x; r < nr; r += nb * blockDim.x) {
+        for (int64_t r = first; r < nr; r += step) {
             const int64_t row = (int64_t)(l2 + (int)(r / ry)) * R.ny + (l1 + (int)(r % ry));
             slo[row] = 0x7f7f7f7f;
             shi[row] = -1;
         }
     }
-    const uint32_t rows = (uint32_t)ey * (uint32_t)ez;
-    const uint32_t nw = (uint32_t)nb * (blockDim.x / 64);
-    const uint32_t w0 = __builtin_amdgcn_readfirstlane((uint32_t)b * (blockDim.x / 64) + (threadIdx.x >> 6));
-    const int lane = threadIdx.x & 63;
-    // row r = k ey + j; the stride nw advances (j, k) by (nw % ey, nw / ey)
-    // with a carry, so only the first row of a wavefront needs a division
-    const uint32_t dk = nw / (uint32_t)ey, dj = nw - dk * (uint32_t)ey;
-    const uint32_t k0 = w0 / (uint32_t)ey, j0 = w0 - k0 * (uint32_t)ey;
-    const int64_t sy = R.nx, sz = (int64_t)R.nx * R.ny;
-    for (int comp = 0; comp < 4; ++comp) {
-        T *dst = src_ptr<T>(R, set_c, comp) + nid(R, l0, l1, l2);
-        T *dlo = R.compensated ? srclo_ptr<T>(R, set_c, comp) + nid(R, l0, l1, l2) : nullptr;
-        uint32_t j = j0, k = k0;
-        for (uint32_t r = w0; r < rows; r += nw) {
-            const int64_t row = (int64_t)k * sz + (int64_t)j * sy;
-            for (int i = lane; i < ex; i += 64) {
-                dst[row + i] = (T)0;
-                if (dlo)
-                    dlo[row + i] = (T)0;
-            }
-            j += dj;
-            k += dk;
-            if (j >= (uint32_t)ey) {
-                j -= (uint32_t)ey;
-                ++k;
-            }
+    const BoxNodes box(l0, l1, l2, ex, ey, ez);
+    const bool all = box.tot * 4 * (int64_t)sizeof(T) <= kZeroAll;
+    int i, j, k;
+    auto marked = [&](int64_t t) {
+        box.node(t, i, j, k);
+        return all || node_marked(R, s, 2, i, j, k);
+    };
+    int64_t t = first;
+    bool next = t < box.tot && marked(t);
+    while (t < box.tot) {
+        const bool now = next;
+        const int64_t at = nid(R, i, j, k);
+        t += step;  // the next node's marks load before this node's stores
+        next = t < box.tot && marked(t);
+        if (!now)
+            continue;
+#pragma unroll
+        for (int comp = 0; comp < 4; ++comp) {
+            src_ptr<T>(R, set_c, comp)[at] = (T)0;
+            if (R.compensated)
+                srclo_ptr<T>(R, set_c, comp)[at] = (T)0;
         }
     }
 }
@@ -860,26 +922,6 @@ __device__ inline void vertex_eb(const RunDev &R, int64_t s, int i, int j, int k
         E[c] = -((double)Ap[c][c0] - (double)An[c][c0]) / R.dt - g[c];
 }
 
-// Is node (i, j, k) a corner of an active cell whose sort tile holds a
-// particle at step s?  The push of step s-1 (or the load) marks the tiles of
-// the cells its particles end in with s; a node's cells are i-1..i on each
-// axis, within the active range 1..n-3.
-__device__ inline bool node_needed(const RunDev &R, int64_t s, int i, int j, int k)
-{
-    const uint32_t want = (uint32_t)s;
-    const int c0[3] = {max(i - 1, 1), max(j - 1, 1), max(k - 1, 1)};
-    const int c1[3] = {min(i, R.nx - 3), min(j, R.ny - 3), min(k, R.nz - 3)};
-    const int tx0 = (int)fdiv((uint32_t)c0[0], R.tdiv[0]), tx1 = (int)fdiv((uint32_t)c1[0], R.tdiv[0]);
-    const int ty0 = (int)fdiv((uint32_t)c0[1], R.tdiv[1]), ty1 = (int)fdiv((uint32_t)c1[1], R.tdiv[1]);
-    const int tz0 = (int)fdiv((uint32_t)c0[2], R.tdiv[2]), tz1 = (int)fdiv((uint32_t)c1[2], R.tdiv[2]);
-    for (int tz = tz0; tz <= tz1; ++tz)
-        for (int ty = ty0; ty <= ty1; ++ty)
-            for (int tx = tx0; tx <= tx1; ++tx)
-                if (R.tile_flag[((int64_t)tz * R.ntile[1] + ty) * R.ntile[0] + tx] == want)
-                    return true;
-    return false;
-}
-
 // E, B over the active-particle box of the last push, where a particle
 // gathers (FACES: see vertex_eb).
 template <typename T, bool FACES>
@@ -897,25 +939,11 @@ struct VertexFields {
                 return;
         }
         constexpr int V = 16 / sizeof(T);
-        const int64_t ex = hi[0] - lo[0] + 1, ey = hi[1] - lo[1] + 1, ez = hi[2] - lo[2] + 1;
-        const int64_t tot = ex * ey * ez;
-        // 32-bit decoding by multiply-high when exact (t * max(ex, ey) < 2^32)
-        const bool fast = (uint64_t)tot * (uint64_t)(ex > ey ? ex : ey) < (1ull << 32);
-        const FastDiv fx = fast_div((uint32_t)ex), fy = fast_div((uint32_t)ey);
-        for (int64_t t = (int64_t)blk.id * blockDim.x + threadIdx.x; t < tot; t += (int64_t)blk.n * blockDim.x) {
+        const BoxNodes box(lo[0], lo[1], lo[2], hi[0] - lo[0] + 1, hi[1] - lo[1] + 1, hi[2] - lo[2] + 1);
+        for (int64_t t = (int64_t)blk.id * blockDim.x + threadIdx.x; t < box.tot; t += (int64_t)blk.n * blockDim.x) {
             int i, j, k;
-            if (fast) {
-                const uint32_t t32 = (uint32_t)t, row = fdiv(t32, fx);
-                const uint32_t kk = fdiv(row, fy);
-                i = lo[0] + (int)(t32 - row * (uint32_t)ex);
-                j = lo[1] + (int)(row - kk * (uint32_t)ey);
-                k = lo[2] + (int)kk;
-            } else {
-                i = lo[0] + (int)(t % ex);
-                j = lo[1] + (int)((t / ex) % ey);
-                k = lo[2] + (int)(t / (ex * ey));
-            }
-            if (!node_needed(R, s, i, j, k))
+            box.node(t, i, j, k);
+            if (!node_marked(R, s, 0, i, j, k))
                 continue;  // no particle of this step gathers at this node
             double E[3], B[3];
             vertex_eb<T, FACES>(R, s, i, j, k, E, B);
