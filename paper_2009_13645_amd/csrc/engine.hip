@@ -3,9 +3,11 @@
 // boost and the NSFD/Mur coefficients, carves the caller's device arena,
 // and enqueues the step pipeline on the caller's stream:
 //
-//   sweep (A, phi; clears the stale source set) -> Mur -> vertex E,B on the
-//   active-particle box -> gather/push/deposit -> bin+sort -> radiated
-//   power -> bookkeeping (step counter, particle buffer).
+//   sweep (A, phi) -> Mur faces, clearing of the stale source set, vertex E,B
+//   around the particles, plane power and spectrum -> gather/push/deposit and
+//   Mur edges -> box reduction and the step's end (power, step counter,
+//   particle buffer; in the next sweep's launch when no sort follows) ->
+//   bin+sort.
 //
 // Every kernel reads the step number from device memory, so one step is
 // captured once into a HIP graph and replayed for the following steps.

@@ -8,11 +8,12 @@
 //    z-averaged value psi-bar of every column (plus a one-column halo ring)
 //    goes through a double-buffered LDS plane, so psi^n is read from HBM
 //    about once.  The source of the step (node-averaged edge current, or
-//    rho) is read only inside the bounding box of the last deposit.
+//    rho) is read only on the x range that the last deposit may have touched
+//    in each (plane, row).
 //  * Mur: Mur absorbing boundaries (sec. "Boundary Truncation"), one thread
 //    per boundary face node.  Faces use the printed first/second-order
-//    updates with permuted axes; further workgroups of the face launch clear
-//    the other source set inside its own box for the coming deposit.  Edges
+//    updates with permuted axes; further workgroups clear the other source
+//    set for the coming deposit.  Edges
 //    and corners (MurEdge, mur_dev.hpp) follow in a later launch: they solve
 //    the sum of the first-order conditions of their faces discretised at the
 //    centre of the 2x2 (2x2x2) node stencil, reading the new face values (a
@@ -20,6 +21,9 @@
 //    reads race-free.
 //  * VertexFields: E and B at vertices (sec. "Field Evaluation"):
 //    E = -(A^{n+1} - A^n)/dt - grad phi, B = mean of curl A^n and curl A^{n+1}.
+//  * StepFields: in a run of its own the Mur faces, the clearing, the vertex
+//    fields, the power's partial sums and the plane's spectrum are one launch;
+//    grouped steps launch Mur, then VertexPower.
 #include "mithra_dev.hpp"
 #include "mur_dev.hpp"
 #include <algorithm>

@@ -12,14 +12,15 @@
 // is the particle ids).
 //
 // Method: the keys are written in the previous order (the push writes the
-// key of rank p at p, coalesced), then an LSD radix sort with 8-bit digits
-// and stable passes runs on (key, slot) pairs.  The value carried is the
+// key of rank p at p, coalesced), then an LSD radix sort with stable passes
+// over 8-bit digits (up to 10 bits in runs of their own of up to 2^18
+// particles: k_wide_*) runs on (key, slot) pairs.  The value carried is the
 // particle's slot in the buffer the next push reads (slot_in), so the
 // push reaches the state without looking the slot up.  Each pass is a
 // per-block digit histogram, 256 independent per-digit scans over the
 // blocks, and a stable scatter that ranks equal digits within a wavefront
-// with ballots.  Finally the particle state is gathered into the other
-// buffer in sorted order.  No library sort and no memset: every pass is a
+// with ballots.  The state itself is not moved here: the next push reads it
+// through the sorted slots.  No library sort and no memset: every pass is a
 // plain kernel, so the pipeline can be captured in a graph.
 #include "mithra_dev.hpp"
 

@@ -542,14 +542,14 @@ struct BoxReduceStep {
 };
 
 // The box reductions, then the end of the step: the step's radiated power
-// from the vertex launch's partial sums (when the run records it) and the
+// from the step-fields launch's partial sums (when the run records it) and the
 // bookkeeping (particle buffer, step counter).  For a single run whose sort,
 // when the step has one, runs as separate pass kernels: those read the sort
 // range and the slots, not the step counter or the buffer index, so the
 // step may end before them and no launch follows the sort.  After a push that
 // no sort follows, one workgroup of the next step's sweep does it
 // (SweepWithTail) when that step is enqueued with this one; else it is a
-// launch.  Grouped steps keep the separate end: there a member on its last
+// launch.  Grouped steps end after the sort (EndStep): a member on its last
 // step skips the stages that come after its step counter has reached the
 // target.
 __device__ inline void end_step(const RunDev &R)

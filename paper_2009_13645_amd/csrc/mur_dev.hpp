@@ -59,7 +59,7 @@ __device__ double solve_summed(const RunDev &R, const Lv<T> &L, const int p[3], 
 }
 
 // The face and interior nodes of an edge's or a corner's stencil already
-// hold their n+1 values when this runs (the sweep and the face kernel come
+// hold their n+1 values when this runs (the sweep and the faces' launch come
 // first), so they are read; a corner recomputes its three edge neighbours.
 template <typename T>
 __device__ double edge_np1(const RunDev &R, const Lv<T> &L, const int p[3], const int *ax, const int *sd)
@@ -101,12 +101,12 @@ __device__ double corner_np1(const RunDev &R, const Lv<T> &L, const int p[3], co
 
 // Edge and corner nodes of the boundary (one thread each, per component):
 // the summed first-order conditions of their faces (solve_summed), with the
-// face values the face kernel has just written; a corner recomputes its
-// three edge neighbours.  Not in the face kernel: this path needs far more
+// face values the faces' launch has just written; a corner recomputes its
+// three edge neighbours.  Not beside the faces: this path needs far more
 // registers than the face path, and in one kernel it set the face threads'
 // occupancy too.  A single run's step carries these workgroups at the end
-// of the push launch (PushThenEdges); grouped steps and the sweep-shape
-// tuners launch them on their own after the face kernel.
+// of the push launch (PushThenEdges); grouped steps run them beside the box
+// reductions after the pushes, the sweep-shape tuners on their own.
 template <typename T>
 struct MurEdge {
     static constexpr int kThreads = 256;
