@@ -94,7 +94,6 @@ struct Sweep {
 
         const int64_t s = R.ctl->step;
         const int set_r = (int)(s & 1);
-        const bool update = (comp < 3) || R.space_charge;
 
         const int lx = threadIdx.x % TX, ly = threadIdx.x / TX;
         const int i = tile_x * TX + lx;
@@ -167,7 +166,7 @@ struct Sweep {
                     hpf = cur[(int64_t)(k + 2) * plane + hcol];
             }
             T pm = 0, sv = 0;
-            if (valid && update) {
+            if (valid) {
                 pm = prev[c];
                 if (src_col && k >= rlo[2] && k <= rhi[2] + 1)
                     sv = src_value<T>(R, comp, set_r, c, back);
@@ -187,7 +186,7 @@ struct Sweep {
                     buf[hy + 1][hx + 1] = cA * (hqm + hqp) + c1A * hq0;
             }
             __syncthreads();
-            if (valid && update) {
+            if (valid) {
                 if constexpr (kDiffForm<T>) {
                     T(*cbuf)[TX + 2] = sbc[k & 1];
                     const T c0 = cbuf[ly + 1][lx + 1];
@@ -289,10 +288,8 @@ struct SweepVec {
         lb /= nty;
         const int chunk = (int)(lb % nch);
         const int comp = (int)(lb / nch);
-        if (comp >= 4)
+        if (comp >= (R.space_charge ? 4 : 3))
             return;  // grid larger than the tiling (never for the launchers here)
-        if (comp == 3 && !R.space_charge)
-            return;  // phi is not advanced without space charge (uniform per workgroup)
         const int64_t s = OWN && tail ? R.ctl->next_step : R.ctl->step;
         // the component is a compile-time constant inside the body, so the
         // source loads of the other components do not exist there
@@ -1260,12 +1257,20 @@ __host__ __device__ inline int64_t seed_blocks_of(const RunDev &R)
 // host launchers
 // ---------------------------------------------------------------------------
 
+// Potentials that a sweep advances: phi only with space charge.  It is the
+// slowest index of the tiles, of which each XCD takes a contiguous eighth, so
+// workgroups for a phi that is not advanced would leave two of the eight idle:
+// 72 x 56 x 136 FP64 without space charge 44.7 -> 42.3 us a step, 64 x 64 x 256
+// FP64 71.6 -> 67.9, 128 x 128 x 1024 FP32 302 -> 295, 64 x 64 x 2800 FP64 454 ->
+// 452 (bound by its bytes on any number of XCDs).
+static int64_t sweep_components(const RunDev &R) { return R.space_charge ? 4 : 3; }
+
 template <typename T, int TX, int TY, int TZ>
 static hipError_t launch_sweep_t(const RunDev &R, hipStream_t st)
 {
     const int64_t ntx = (R.nx + TX - 1) / TX, nty = (R.ny + TY - 1) / TY;
     const int64_t nch = (R.nz - 2 + TZ - 1) / TZ;
-    const int64_t nb = ntx * nty * nch * 4;
+    const int64_t nb = ntx * nty * nch * sweep_components(R);
     hipLaunchKernelGGL((k_run<Sweep<T, TX, TY, TZ>>), dim3((unsigned)nb), dim3(TX * TY), 0, st, R);
     return hipGetLastError();
 }
@@ -1276,7 +1281,7 @@ static hipError_t launch_sweep_vec_t(const RunDev &R, int tail, hipStream_t st)
     constexpr int TW = TXV * V;
     const int64_t ntx = (R.nx + TW - 1) / TW, nty = (R.ny + TY - 1) / TY;
     const int64_t nch = (R.nz - 2 + TZ - 1) / TZ;
-    const dim3 grid((unsigned)(ntx * nty * nch * 4 + tail)), block(TXV * TY);
+    const dim3 grid((unsigned)(ntx * nty * nch * sweep_components(R) + tail)), block(TXV * TY);
     if constexpr (sizeof(T) == 4) {
         if (R.compensated) {
             hipLaunchKernelGGL((k_run<SweepWithTail<SweepVec<T, V, TXV, TY, TZ, true>>, int>), grid, block, 0, st, R,
@@ -1461,7 +1466,7 @@ namespace mithra {
 
 int64_t sweep_blocks(const RunDev &R, int shape)
 {
-    return sweep_tiles(R.nx, R.ny, R.nz, R.precision, sweep_effective_shape(R, shape));
+    return sweep_tiles(R.nx, R.ny, R.nz, R.precision, sweep_effective_shape(R, shape)) / 4 * sweep_components(R);
 }
 
 template <typename T, int TX, int TY, int TZ>
