@@ -358,7 +358,7 @@ extern "C" int mithra_init_grid(const mithra_grid_desc *d, void *dev_arena, size
     R.gbc = R.gamma0 * R.beta0 * kC;
     R.b0c = R.beta0 * kC;
     R.ek = kQe * R.dtb / (2.0 * kMe * kC);
-    R.ak = -kQe * R.dtb / (2.0 * kMe);
+    R.ak = -kQe * R.dtb;
     R.cdtb = kC * R.dtb;
     R.B_per_K = 2.0 * kPi * kMe * kC / (kQe * d->lambda_u);
     R.und_type = d->und_type;

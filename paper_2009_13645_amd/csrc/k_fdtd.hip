@@ -1148,9 +1148,9 @@ __global__ __launch_bounds__(256) void k_spec_reduce(RunDev R, double *out)
 // ---------------------------------------------------------------------------
 
 // The incident wave on one plane: everything but the radius is uniform on
-// it.  F(r2) = a (without the polarisation) exp(-r2 iw2) cos(ph + curv r2).
+// it.  F(r2) = a (without the polarisation) exp(-r2 / w2) cos(ph + curv r2).
 struct SeedPlane {
-    double a, iw2, ph, curv;
+    double a, w2, ph, curv;
 };
 
 __device__ inline SeedPlane seed_plane(const RunDev &R, int k, double t)
@@ -1161,7 +1161,7 @@ __device__ inline SeedPlane seed_plane(const RunDev &R, int k, double t)
     const double f = kC / lam, tp = R.seed_ctau / kC * D, t0 = R.seed_ct0 / kC * D;
     const double d = t - (z - z2) / kC - t0;
     const double ln2 = 0.69314718055994530942;
-    SeedPlane P{R.seed_a0 * kMe * kC / kQe, 0.0, 2.0 * kPi * f * d + R.seed_cep, 0.0};
+    SeedPlane P{R.seed_a0 * kMe * kC / kQe, 1.0, 2.0 * kPi * f * d + R.seed_cep, 0.0};
     // the signal's envelope (the carrier is the cosine of F)
     const double gauss = exp(-2.0 * ln2 * d * d / (tp * tp));
     if (R.seed_signal == 0)
@@ -1175,7 +1175,7 @@ __device__ inline SeedPlane seed_plane(const RunDev &R, int k, double t)
         const double l = z - R.seed_zf;
         const double w = R.seed_w0 * sqrt(1.0 + (l / zR) * (l / zR));
         P.a *= R.seed_w0 / w;
-        P.iw2 = 1.0 / (w * w);
+        P.w2 = w * w;
         P.curv = -0.5 * (2.0 * kPi / lam) * l / (l * l + zR * zR);
         P.ph += atan(l / zR);
     }
@@ -1214,7 +1214,7 @@ struct SeedInject {
             const SeedPlane p = P[pl];
             double v = p.a * cos(p.ph + p.curv * r2);
             if (R.seed_type == 1)
-                v *= exp(-r2 * p.iw2);
+                v *= exp(-r2 / p.w2);
             F[pl][ej][ei] = v;
         }
         __syncthreads();

@@ -126,7 +126,7 @@ struct PushDeposit {
                         Be[a] += Bg[a];
                     }
                     boris(R, u, Ee, Be);
-                    const double ig = rsqrt(1.0 + u[0] * u[0] + u[1] * u[1] + u[2] * u[2]);
+                    const double ig = 1.0 / sqrt(1.0 + u[0] * u[0] + u[1] * u[1] + u[2] * u[2]);
                     for (int a = 0; a < 3; ++a)
                         r[a] = r[a] + R.cdtb * u[a] * ig;
                 };

@@ -96,7 +96,7 @@ struct RunDev {
     double theta, sth, cth;        // polarisation angle, its sine and cosine
     double half_turns;             // 2 / lambda_u: undulator phase in half turns per metre
     double gbc, b0c;               // gamma0 beta0 c, beta0 c
-    double ek, ak, cdtb;           // Boris: e dt_b / (2 m c), -e dt_b / (2 m); c dt_b
+    double ek, ak, cdtb;           // Boris: e dt_b / (2 m c), -e dt_b; c dt_b
     int und_type;     // 0 planar, 1 helical, 2 optical plane wave, 3 optical Gaussian beam
     int und_ext;      // 1: the external field needs the general path (arrays or optical)
     double Kund, lam_u; // undulator parameter (optical: a0) and period (optical: half the wavelength)

@@ -15,20 +15,14 @@
 
 namespace mithra {
 
-// The push is short of VALU issue, so it avoids what the
-// compiler expands at length: an FP64 division (11 instructions), sincos of
-// an argument that may need a many-word reduction (its code and registers
-// are there for every particle), and arithmetic on values that are the same
-// for the whole run (R.gbc, R.ek and so on come from the host).
-
-// 1 / x for a normal x: the hardware estimate and two Newton steps (relative
-// error below 1.5 x 2^-53, one rounding more than the division's).
-__device__ inline double recip(double x)
-{
-    double r = __builtin_amdgcn_rcp(x);
-    r = fma(r, fma(-x, r, 1.0), r);
-    return fma(r, fma(-x, r, 1.0), r);
-}
+// The push is short of VALU issue, so it avoids what the compiler expands at
+// length where the result is rounded no worse without it: sincos of an argument
+// that may need a many-word reduction (its code and registers are there for
+// every particle), FP64 divisions by a mesh spacing (quotient), and arithmetic
+// on values that are the same for the whole run (R.gbc, R.ek and so on come
+// from the host).  The divisions and square roots of the Boris step and of
+// cosh and sinh stay rounded ones: from the hardware estimates and Newton
+// steps they carried one rounding more.
 
 // a / b rounded as the division rounds it, from y = 1 / b rounded to FP64:
 // the first correction makes the quotient faithful, and the correction of a
@@ -45,7 +39,7 @@ __device__ inline double quotient(double a, double b, double y)
 __device__ inline void cosh_sinh(double x, double &ch, double &sh)
 {
     const double em = expm1(fabs(x));
-    const double h = 0.5 * em * recip(1.0 + em);
+    const double h = 0.5 * em / (1.0 + em);
     sh = copysign(h * (2.0 + em), x);
     ch = fma(h, em, 1.0);
 }
@@ -113,8 +107,8 @@ __device__ inline void undulator_field(const RunDev &R, double x, double y, doub
 // ~6e-5 at the far end of the gap
 __device__ inline double gap_window(double dz, double inv_g)
 {
-    const double c = cospi(dz * inv_g);
-    return 0.35875 + 0.48829 * c + 0.14128 * (2.0 * c * c - 1.0) + 0.01168 * ((4.0 * c * c - 3.0) * c);
+    const double t = dz * inv_g;
+    return 0.35875 + 0.48829 * cospi(t) + 0.14128 * cospi(2.0 * t) + 0.01168 * cospi(3.0 * t);
 }
 
 // longitudinal profile of the planar pattern of a module array at lab z'
@@ -159,12 +153,13 @@ __device__ inline void array_profile(const RunDev &R, double zl, double &gB, dou
 __device__ inline void array_planar(const RunDev &R, double x, double y, double zl, double sth, double cth,
                                     double Bl[3])
 {
-    double gB, hB, ch, sh;
+    double gB, hB;
     array_profile(R, zl, gB, hB);
-    cosh_sinh(R.ku * (x * sth + y * cth), ch, sh);
-    Bl[0] = gB * ch * sth;
-    Bl[1] = gB * ch * cth;
-    Bl[2] = hB * sh;
+    const double a = R.ku * (x * sth + y * cth);
+    const double Bperp = gB * cosh(a);
+    Bl[0] = Bperp * sth;
+    Bl[1] = Bperp * cth;
+    Bl[2] = hB * sinh(a);
 }
 
 // optical pulse signature with unit amplitude (modulated Neumann scaled by
@@ -279,12 +274,12 @@ __device__ inline void boris(const RunDev &R, double u[3], const double E[3], co
     double t1[3];
     for (int a = 0; a < 3; ++a)
         t1[a] = u[a] - R.ek * E[a];
-    const double alpha = R.ak * rsqrt(1.0 + t1[0] * t1[0] + t1[1] * t1[1] + t1[2] * t1[2]);
+    const double alpha = R.ak / (2.0 * kMe * sqrt(1.0 + t1[0] * t1[0] + t1[1] * t1[1] + t1[2] * t1[2]));
     double t2[3];
     t2[0] = t1[0] + alpha * (t1[1] * B[2] - t1[2] * B[1]);
     t2[1] = t1[1] + alpha * (t1[2] * B[0] - t1[0] * B[2]);
     t2[2] = t1[2] + alpha * (t1[0] * B[1] - t1[1] * B[0]);
-    const double f = 2.0 * alpha * recip(1.0 + alpha * alpha * (B[0] * B[0] + B[1] * B[1] + B[2] * B[2]));
+    const double f = 2.0 * alpha / (1.0 + alpha * alpha * (B[0] * B[0] + B[1] * B[1] + B[2] * B[2]));
     const double s[3] = {f * B[0], f * B[1], f * B[2]};
     u[0] = t1[0] + (t2[1] * s[2] - t2[2] * s[1]) - R.ek * E[0];
     u[1] = t1[1] + (t2[2] * s[0] - t2[0] * s[2]) - R.ek * E[1];
