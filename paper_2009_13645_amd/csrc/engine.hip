@@ -820,6 +820,12 @@ static int copy_out(mithra_handle h, const std::vector<ReadOut> &outs, bool chec
     char *ctl = h->stage + 2 * kStageHalf;
     if (check_nan)
         HIPCHK(h, hipMemcpyAsync(ctl, h->R.ctl, sizeof(Ctl), hipMemcpyDeviceToHost, h->stream));
+    if (outs.empty()) {  // no copy below waits for the flag's
+        HIPCHK(h, hipStreamSynchronize(h->stream));
+        if (check_nan && ((const Ctl *)ctl)->nan_flag)
+            return fail(h, MITHRA_ENUMERIC, "non-finite value detected by the diagnostics");
+        return MITHRA_OK;
+    }
     auto drain = [&](int k) -> int {
         if (!pending[k])
             return MITHRA_OK;
@@ -886,7 +892,8 @@ extern "C" int mithra_read_fields(mithra_handle h, int field_id, int dtype, void
     if (field_id <= MITHRA_FIELD_BZ) {
         if (S == 0) {
             rc = copy_out(h, {}, true);
-            memset(host_out, 0, bytes);
+            if (!rc)
+                memset(host_out, 0, bytes);
             return rc;
         }
         HIPCHK(h, launch_read_vertex(R, S - 1, field_id, tmp, esz == 8, h->stream));
