@@ -811,8 +811,7 @@ static int copy_out(mithra_handle h, const std::vector<ReadOut> &outs, bool chec
         if (flag)
             return fail(h, MITHRA_ENUMERIC, "non-finite value detected by the diagnostics");
         for (const ReadOut &o : outs)
-            HIPCHK(h, hipMemcpyAsync(o.dst, o.src, o.bytes, hipMemcpyDeviceToHost, h->stream));
-        HIPCHK(h, hipStreamSynchronize(h->stream));
+            HIPCHK(h, hipMemcpy(o.dst, o.src, o.bytes, hipMemcpyDeviceToHost));
         return MITHRA_OK;
     }
     std::vector<Part> parts[2];
