@@ -406,7 +406,9 @@ int mithra_batch_destroy(mithra_batch b);
 /* Message of the last error on this handle (never NULL). */
 const char *mithra_last_error(mithra_handle h);
 
-/* Release the host-side state.  The arena stays the caller's. */
+/* Release the host-side state.  The arena stays the caller's.  Does not wait
+ * for other handles' work; the process's last handle releases the pinned
+ * memory of the read calls, which may wait for the device. */
 int mithra_destroy(mithra_handle h);
 
 #ifdef __cplusplus

@@ -1,5 +1,6 @@
 """Reads through a handle's pinned memory (a handle has it after 48 read calls
-or MiB): the non-finite report, calls that return nothing, members of a batch."""
+or MiB): the non-finite report, calls that return nothing, its release, members
+of a batch."""
 import numpy as np
 import pytest
 import torch  # noqa: F401
@@ -39,6 +40,26 @@ def test_non_finite_run_is_reported_by_every_read():
             read()
         assert ei.value.code == -5
     assert e._L.mithra_read_particles(e._h, None, None, None, None) == -5
+
+
+def test_destroy_does_not_wait_for_another_handle():
+    a, b = _run(4096, -1e-15, 64), _run(4096, -1e-15, 64)
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        c = _run(4096, -1e-15, 64)  # on the other stream
+    for e in (a, b):
+        _stage(e)
+    torch.cuda.synchronize()
+    c.step(8000)  # some 200 ms of work
+    done = torch.cuda.Event()
+    done.record(side)
+    a.close()
+    assert not done.query()  # c still steps
+    field = b.read_field("Ax")
+    _stage(c)
+    assert not np.any(field) and np.all(np.isfinite(c.read_field("Ax")))
+    b.close()
+    c.close()
 
 
 def test_members_of_a_batch():
