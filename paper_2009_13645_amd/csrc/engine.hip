@@ -216,6 +216,7 @@ struct mithra_engine {
     int64_t steps = 0;
     bool loaded = false;
     int sweep_shape = 0;
+    int default_shape = 0;  // the sweep shape at init
     int32_t *cell_by_id = nullptr;
     // captured steps: one step without and with the sort launches; a run of
     // steps starting at each sort phase (step mod sort_every)
@@ -563,6 +564,7 @@ extern "C" int mithra_init_grid(const mithra_grid_desc *d, void *dev_arena, size
     const char *sh = getenv("MITHRA_SWEEP_SHAPE");
     if (sh)
         h->sweep_shape = atoi(sh) % sweep_shape_count();
+    h->default_shape = h->sweep_shape;
     R.xface_fused = sweep_fuses_xfaces(R, h->sweep_shape);
     *out = h;
     return MITHRA_OK;
@@ -1386,8 +1388,8 @@ extern "C" int mithra_set_sweep_shape(mithra_handle h, int shape)
         return MITHRA_EINVAL;
     if (h->batched)
         return fail(h, MITHRA_ESTATE, "the run belongs to a batch: its sweep shape is fixed");
-    if (h->R.seed_on && sweep_fuses_xfaces(h->R, shape))
-        return fail(h, MITHRA_EINVAL, "a seeded run takes its default sweep shape or a scalar one");
+    if (h->R.seed_on && shape != h->sweep_shape && shape != h->default_shape && sweep_fuses_xfaces(h->R, shape))
+        return fail(h, MITHRA_EINVAL, "a seeded run takes its own sweep shape, its default one or a scalar one");
     h->sweep_shape = shape;
     h->R.xface_fused = sweep_fuses_xfaces(h->R, shape);
     drop_graphs(h);
