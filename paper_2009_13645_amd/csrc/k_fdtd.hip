@@ -1007,20 +1007,36 @@ struct PlanePowerFinal {
     }
 };
 
-// Workgroups of the vertex fields (the same count on host and device): an
-// eighth of what one node per thread needs, 1024 at most.  The particle box
-// is a small part of the grid (the grid holds the radiation around the
-// bunch); workgroups past it find no node to do, but go through dispatch and
-// hold the slots that the working ones and the boundary's wait for.  The
-// grid-stride loop covers a box as large as the grid.  Single runs, the
-// launch that holds them (StepFields), with up to 8192 / 2048 / 1024
-// workgroups: 128 x 128 x 1024 nodes FP32 89 / 79 / 80 us, FP64 133 / 123 /
-// 122, 64 x 64 x 2800 FP64 143 / 133 / 131, 64 x 64 x 384 25 / 21 / 19.
+// Workgroups of the vertex fields: an eighth of what one node per thread
+// needs, 1024 at most.  The particle box is usually a small part of the grid
+// (the grid holds the radiation around the bunch); workgroups past it find no
+// node to do, but go through dispatch and hold the slots that the working ones
+// and the boundary's wait for.  The grid-stride loop covers a box as large as
+// the grid.  Single runs, the launch that holds them (StepFields), with up to
+// 8192 / 2048 / 1024 workgroups: 128 x 128 x 1024 nodes FP32 89 / 79 / 80 us,
+// FP64 133 / 123 / 122, 64 x 64 x 2800 FP64 143 / 133 / 131, 64 x 64 x 384
+// 25 / 21 / 19.
 __host__ __device__ inline int64_t vertex_blocks_of(const RunDev &R)
 {
     const int64_t inner = (int64_t)(R.nx - 2) * (R.ny - 2) * (R.nz - 2);
     const int64_t b = (inner + 255) / 256 / 8;
     return b < 1 ? 1 : (b > 1024 ? 1024 : b);
+}
+
+// A run of its own: one node per thread up to two workgroups a CU, which are
+// free slots on a device that runs nothing else.  With particles over the
+// whole grid an eighth left CUs idle and each thread eight nodes in sequence:
+// 32 x 32 x 64 FP32 50.2 -> 43.0 us a step (48.9 with one node per thread
+// throughout, before StepFields), FP64 63.0 -> 54.5, 24 x 24 x 400 FP32 60.7 ->
+// 49.5, 48 x 48 x 96 FP64 62.3 -> 54.4, 64 x 64 x 128 FP32 123 -> 119; with the
+// bunch in a sixteenth of the grid across the same (34.7 and 39.2 us both).  One
+// node per thread up to 1024 workgroups: 64 x 64 x 128 FP64 156 against 153.
+static int64_t vertex_blocks_own(const RunDev &R)
+{
+    const int64_t inner = (int64_t)(R.nx - 2) * (R.ny - 2) * (R.nz - 2);
+    const int64_t full = (inner + 255) / 256;
+    const int64_t least = full < 512 ? full : 512, eighth = vertex_blocks_of(R);
+    return eighth > least ? eighth : least;
 }
 
 // ---------------------------------------------------------------------------
@@ -1419,7 +1435,7 @@ hipError_t launch_mur(const RunDev &R, hipStream_t st)
 hipError_t launch_step_fields(const RunDev &R, hipStream_t st)
 {
     const unsigned blocks = (unsigned)(StepFields<float>::power_blocks(R) + spectrum_blocks_of(R) + mur_blocks_of(R) +
-                                       vertex_blocks_of(R));
+                                       vertex_blocks_own(R));
     if (R.precision == 32)
         hipLaunchKernelGGL((k_run<StepFields<float>>), dim3(blocks), dim3(256), 0, st, R);
     else
