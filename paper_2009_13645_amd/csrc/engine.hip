@@ -31,7 +31,7 @@
 namespace mithra {
 hipError_t launch_sweep(const RunDev &R, int shape, hipStream_t st, int tail = 0);
 int sweep_shape_count();
-int sweep_default_shape(int nx, int ny, int nz, int precision);
+int sweep_default_shape(int nx, int ny, int nz, int precision, int space_charge);
 int sweep_effective_shape(const RunDev &R, int shape);
 hipError_t launch_mur(const RunDev &R, hipStream_t st);
 int sweep_fuses_xfaces(const RunDev &R, int shape);
@@ -560,7 +560,7 @@ extern "C" int mithra_init_grid(const mithra_grid_desc *d, void *dev_arena, size
         box_slot_empty(&slots[16 * b]);
     HIPCHK(h, hipMemcpyAsync(R.boxslot, slots.data(), slots.size() * 4, hipMemcpyHostToDevice, h->stream));
     HIPCHK(h, sync_run(h));
-    h->sweep_shape = sweep_default_shape(d->nx, d->ny, d->nz, d->field_precision);
+    h->sweep_shape = sweep_default_shape(d->nx, d->ny, d->nz, d->field_precision, d->space_charge);
     const char *sh = getenv("MITHRA_SWEEP_SHAPE");
     if (sh)
         h->sweep_shape = atoi(sh) % sweep_shape_count();

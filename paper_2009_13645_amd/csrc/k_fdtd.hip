@@ -1279,14 +1279,14 @@ __host__ __device__ inline int64_t seed_blocks_of(const RunDev &R)
 // 72 x 56 x 136 FP64 without space charge 44.7 -> 42.3 us a step, 64 x 64 x 256
 // FP64 71.6 -> 67.9, 128 x 128 x 1024 FP32 302 -> 295, 64 x 64 x 2800 FP64 454 ->
 // 452 (bound by its bytes on any number of XCDs).
-static int64_t sweep_components(const RunDev &R) { return R.space_charge ? 4 : 3; }
+static int sweep_components(int space_charge) { return space_charge ? 4 : 3; }
 
 template <typename T, int TX, int TY, int TZ>
 static hipError_t launch_sweep_t(const RunDev &R, hipStream_t st)
 {
     const int64_t ntx = (R.nx + TX - 1) / TX, nty = (R.ny + TY - 1) / TY;
     const int64_t nch = (R.nz - 2 + TZ - 1) / TZ;
-    const int64_t nb = ntx * nty * nch * sweep_components(R);
+    const int64_t nb = ntx * nty * nch * sweep_components(R.space_charge);
     hipLaunchKernelGGL((k_run<Sweep<T, TX, TY, TZ>>), dim3((unsigned)nb), dim3(TX * TY), 0, st, R);
     return hipGetLastError();
 }
@@ -1297,7 +1297,7 @@ static hipError_t launch_sweep_vec_t(const RunDev &R, int tail, hipStream_t st)
     constexpr int TW = TXV * V;
     const int64_t ntx = (R.nx + TW - 1) / TW, nty = (R.ny + TY - 1) / TY;
     const int64_t nch = (R.nz - 2 + TZ - 1) / TZ;
-    const dim3 grid((unsigned)(ntx * nty * nch * sweep_components(R) + tail)), block(TXV * TY);
+    const dim3 grid((unsigned)(ntx * nty * nch * sweep_components(R.space_charge) + tail)), block(TXV * TY);
     if constexpr (sizeof(T) == 4) {
         if (R.compensated) {
             hipLaunchKernelGGL((k_run<SweepWithTail<SweepVec<T, V, TXV, TY, TZ, true>>, int>), grid, block, 0, st, R,
@@ -1325,11 +1325,12 @@ int sweep_shape_count() { return 18; }
 // Vector tiles need rows that start on 16 bytes.
 static bool sweep_aligned(int nx, int precision) { return nx % (precision == 32 ? 4 : 2) == 0; }
 
+// tiles of one component
 static int64_t sweep_tiles(int nx, int ny, int nz, int precision, int shape)
 {
     const int *d = kSweepTile[shape];
     const int ty = shape >= 8 && precision == 64 ? d[1] / 2 : d[1];
-    return (int64_t)((nx + d[0] - 1) / d[0]) * ((ny + ty - 1) / ty) * ((nz - 2 + d[2] - 1) / d[2]) * 4;
+    return (int64_t)((nx + d[0] - 1) / d[0]) * ((ny + ty - 1) / ty) * ((nz - 2 + d[2] - 1) / d[2]);
 }
 
 // Default tile of a grid: the least estimated time, in units of one plane of
@@ -1347,18 +1348,22 @@ static int64_t sweep_tiles(int nx, int ny, int nz, int precision, int shape)
 // mean.  Sweep alone, before and after: 64 x 64 x 256 FP64 37.4 -> 21.5 us,
 // 96 x 80 x 192 FP32 31.3 -> 21.4, 24 x 24 x 400 FP32 19.5 -> 8.8, 45 x 51 x
 // 97 FP32 19.9 -> 9.0; in the step of the 128 x 128 x 1024 run FP32 166 -> 162,
-// FP64 309 -> 302.
-int sweep_default_shape(int nx, int ny, int nz, int precision)
+// FP64 309 -> 302.  Without space charge there are three components to count:
+// with four, 4 of 60 grids took another tile and were 15 % from the best one in
+// the mean, with three 2 % (112 x 54 x 167 FP32 14.1 -> 11.6 us, 57 x 25 x 772
+// FP64 23.6 -> 17.5).
+int sweep_default_shape(int nx, int ny, int nz, int precision, int space_charge)
 {
     const bool vec = sweep_aligned(nx, precision);
     const double slots = vec ? 576 : 1500, prologue = vec ? 1.5 : 0.5, row_end = vec ? 24 : 8;
-    const double mb = 4e-6 * nx * ny * nz * (precision / 8);
+    const int comps = sweep_components(space_charge);
+    const double mb = 1e-6 * comps * nx * ny * nz * (precision / 8);
     int best = -1;
     double best_cost = 0;
     for (int s = vec ? 8 : 0; s < (vec ? 18 : 8); ++s) {
         const int *d = kSweepTile[s];
         const double ty = vec && precision == 64 ? d[1] / 2 : d[1], tz = d[2];
-        const double n = (double)sweep_tiles(nx, ny, nz, precision, s) * (s == 5 || s == 12 ? 2 : 1);
+        const double n = (double)comps * sweep_tiles(nx, ny, nz, precision, s) * (s == 5 || s == 12 ? 2 : 1);
         const double cost = std::max(1.0, n / slots) * (tz + prologue) +
                             mb * (3 + 2 / tz + 5 / ty * (1 + 2 / tz) + row_end / d[0]) / 13;
         if (best < 0 || cost < best_cost) {
@@ -1373,7 +1378,9 @@ int sweep_default_shape(int nx, int ny, int nz, int precision)
 // replaced by the grid's default (scalar) tile.
 int sweep_effective_shape(const RunDev &R, int shape)
 {
-    return shape >= 8 && !sweep_aligned(R.nx, R.precision) ? sweep_default_shape(R.nx, R.ny, R.nz, R.precision) : shape;
+    if (shape >= 8 && !sweep_aligned(R.nx, R.precision))
+        return sweep_default_shape(R.nx, R.ny, R.nz, R.precision, R.space_charge);
+    return shape;
 }
 
 int sweep_fuses_xfaces(const RunDev &R, int shape) { return shape >= 8 && sweep_aligned(R.nx, R.precision) ? 1 : 0; }
@@ -1482,7 +1489,7 @@ namespace mithra {
 
 int64_t sweep_blocks(const RunDev &R, int shape)
 {
-    return sweep_tiles(R.nx, R.ny, R.nz, R.precision, sweep_effective_shape(R, shape)) / 4 * sweep_components(R);
+    return sweep_tiles(R.nx, R.ny, R.nz, R.precision, sweep_effective_shape(R, shape)) * sweep_components(R.space_charge);
 }
 
 template <typename T, int TX, int TY, int TZ>
