@@ -36,11 +36,11 @@ int sweep_effective_shape(const RunDev &R, int shape);
 hipError_t launch_mur(const RunDev &R, hipStream_t st);
 int sweep_fuses_xfaces(const RunDev &R, int shape);
 hipError_t launch_step_fields(const RunDev &R, hipStream_t st);
-hipError_t launch_plane_power(const RunDev &R, int step_bias, int kp, double *out, hipStream_t st, int end_step = 0);
+hipError_t launch_plane_power(const RunDev &R, int step_bias, int kp, double *out, hipStream_t st);
 hipError_t launch_spec_reduce(const RunDev &R, double *out, hipStream_t st);
 hipError_t launch_seed_inject(const RunDev &R, hipStream_t st);
 hipError_t launch_gen_bunch(const RunDev &R, const GenParams &P, int pass, double *zrange, hipStream_t st);
-hipError_t launch_push_deposit(const RunDev &R, hipStream_t st, bool box, bool end_step);
+hipError_t launch_push_deposit(const RunDev &R, hipStream_t st, bool ends);
 hipError_t launch_load_deposit(const RunDev &R, hipStream_t st);
 hipError_t launch_bunching(const RunDev &R, double *part, int blocks, hipStream_t st);
 hipError_t launch_read_convert(const RunDev &R, const void *a, const void *lo, void *out, bool out64, hipStream_t st);
@@ -65,8 +65,8 @@ hipError_t launch_vertex_power_group(const Group &g, int64_t total, int precisio
 hipError_t launch_push_group(const Group &g, int64_t total, int precision, int compensated, bool subs, hipStream_t st);
 hipError_t launch_box_edges_group(const Group &g, int64_t total, hipStream_t st);
 hipError_t launch_end_step_group(const Group &g, int64_t total, hipStream_t st);
-hipError_t launch_sort_group(const Group &gs, int64_t total_s, const Group &gd, int64_t total_d, const Group &gp,
-                             int64_t total_p, int max_passes, hipStream_t st);
+hipError_t launch_sort_group(const Group &gs, int64_t total_s, const Group &gd, int64_t total_d, int max_passes,
+                             hipStream_t st);
 int64_t dep_blocks(int64_t np);
 int sort_passes(uint32_t key_inactive);
 int64_t sort_blocks(int64_t n);
@@ -685,7 +685,7 @@ static int enqueue_step_on(mithra_handle h, hipStream_t st, hipEvent_t *ev, int6
     // the sort passes, when the step sorts, follow
     const bool small = sort_ends_step(R);
     const bool leave = more && R.sort_every > 1 && (s + 1) % R.sort_every != 0 && sweep_fuses_xfaces(R, h->sweep_shape);
-    HIPCHK(h, launch_push_deposit(R, st, !small && !leave, !small));
+    HIPCHK(h, launch_push_deposit(R, st, !small && !leave));
     HIPCHK(h, mark(4));
     if (step_sorts(h, s) && !leave)
         HIPCHK(h, launch_sort(R, st, true, 1));
@@ -1601,7 +1601,7 @@ struct mithra_batch_s {
         GroupTab t;
     };
     std::vector<SweepCls> sweep;
-    GroupTab mur[2], mur_edge[2], vertex[2], push[6], box_edges, one, sort_s, sort_d, sort_p;
+    GroupTab mur[2], mur_edge[2], vertex[2], push[6], box_edges, one, sort_s, sort_d;
     int max_passes = 0;
     hipGraphExec_t graph = nullptr;         // one batched step
     hipGraphExec_t graph_nosort = nullptr;  // the same without the sort passes (captured on first use)
@@ -1735,8 +1735,6 @@ static int build_tables(mithra_batch b)
         rc = make_tab(b, all, [](const RunDev &R) { return R.sort_blocks; }, &b->sort_s);
     if (!rc)
         rc = make_tab(b, all, [](const RunDev &) { return (int64_t)256; }, &b->sort_d);
-    if (!rc)
-        rc = make_tab(b, all, [](const RunDev &) { return (int64_t)1; }, &b->sort_p);  // SortRange
     if (rc)
         return rc;
     b->max_passes = 0;
@@ -1783,8 +1781,8 @@ static int enqueue_batch_step(mithra_batch b, hipStream_t st, bool sort)
     BHIPCHK(b, hipStreamWaitEvent(st, b->join, 0));
     BHIPCHK(b, launch_box_edges_group(b->box_edges.g, b->box_edges.total, st));
     if (sort)
-        BHIPCHK(b, launch_sort_group(b->sort_s.g, b->sort_s.total, b->sort_d.g, b->sort_d.total, b->sort_p.g,
-                                     b->sort_p.total, b->max_passes, st));
+        BHIPCHK(b, launch_sort_group(b->sort_s.g, b->sort_s.total, b->sort_d.g, b->sort_d.total, b->max_passes,
+                                     st));
     BHIPCHK(b, launch_end_step_group(b->one.g, b->one.total, st));
     return MITHRA_OK;
 }

@@ -1001,9 +1001,9 @@ struct PlanePower {
 
 struct PlanePowerFinal {
     static constexpr int kThreads = 64;
-    static __device__ void run(const RunDev &R, Blk blk, int step_bias, double *out, int end_step)
+    static __device__ void run(const RunDev &R, Blk blk, int step_bias, double *out)
     {
-        plane_power_final(R, R.ctl->step + step_bias, out, end_step);
+        plane_power_final(R, R.ctl->step + step_bias, out, 0);
     }
 };
 
@@ -1470,13 +1470,13 @@ hipError_t launch_seed_inject(const RunDev &R, hipStream_t st)
     return hipGetLastError();
 }
 
-hipError_t launch_plane_power(const RunDev &R, int step_bias, int kp, double *out, hipStream_t st, int end_step)
+hipError_t launch_plane_power(const RunDev &R, int step_bias, int kp, double *out, hipStream_t st)
 {
     if (R.precision == 32)
         hipLaunchKernelGGL((k_run<PlanePower<float, false>, int, int>), dim3(kPowerBlocks), dim3(256), 0, st, R, step_bias, kp);
     else
         hipLaunchKernelGGL((k_run<PlanePower<double, false>, int, int>), dim3(kPowerBlocks), dim3(256), 0, st, R, step_bias, kp);
-    hipLaunchKernelGGL((k_run<PlanePowerFinal, int, double *, int>), dim3(1), dim3(64), 0, st, R, step_bias, out, end_step);
+    hipLaunchKernelGGL((k_run<PlanePowerFinal, int, double *>), dim3(1), dim3(64), 0, st, R, step_bias, out);
     return hipGetLastError();
 }
 

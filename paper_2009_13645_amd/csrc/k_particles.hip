@@ -579,17 +579,14 @@ hipError_t launch_box_reduce(const RunDev &R, int64_t nblocks, const int32_t *pa
 
 int64_t dep_blocks(int64_t np) { return (np + kDepThreads - 1) / kDepThreads; }
 
-hipError_t launch_push_deposit(const RunDev &R, hipStream_t st, bool box, bool end_step)
+// ends: the box reductions and the end of the step follow here; else the small
+// sort's workgroup or the next step's sweep has them
+hipError_t launch_push_deposit(const RunDev &R, hipStream_t st, bool ends)
 {
     hipError_t e = launch_dep<0>(R, st);
-    if (e != hipSuccess || !box)  // !box: the small sort's workgroup reduces the boxes
+    if (e != hipSuccess || !ends)
         return e;
-    // the boxes are written by a kernel that reads the step number on the
-    // device, like every other stage
-    if (end_step)
-        hipLaunchKernelGGL((k_run<BoxReduceEndStep>), dim3(1), dim3(BoxReduceEndStep::kThreads), 0, st, R);
-    else if (R.np > 0)
-        hipLaunchKernelGGL((k_run<BoxReduceStep>), dim3(1), dim3(BoxReduceStep::kThreads), 0, st, R);
+    hipLaunchKernelGGL((k_run<BoxReduceEndStep>), dim3(1), dim3(BoxReduceEndStep::kThreads), 0, st, R);
     return hipGetLastError();
 }
 

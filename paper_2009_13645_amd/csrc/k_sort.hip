@@ -779,14 +779,12 @@ hipError_t launch_sort(const RunDev &R, hipStream_t st, bool keys_ready, int ste
 namespace mithra {
 
 // gs: members with sort_blocks workgroups; gd: 256 workgroups each (one
-// per digit); the key range was set by the box reduction before (gp unused)
-hipError_t launch_sort_group(const Group &gs, int64_t total_s, const Group &gd, int64_t total_d, const Group &gp,
-                             int64_t total_p, int max_passes, hipStream_t st)
+// per digit); the key range was set by the box reduction before
+hipError_t launch_sort_group(const Group &gs, int64_t total_s, const Group &gd, int64_t total_d, int max_passes,
+                             hipStream_t st)
 {
-    if (total_p <= 0)
+    if (total_s <= 0)
         return hipSuccess;
-    (void)gp;
-    (void)total_p;
     for (int ps = 0; ps < max_passes; ++ps) {
         hipLaunchKernelGGL((k_group<RadixHistRun, int>), dim3((unsigned)total_s), dim3(kSortThreads), 0, st, gs, ps);
         hipLaunchKernelGGL((k_group<DigitScanRun, int>), dim3((unsigned)total_d), dim3(256), 0, st, gd, ps);
