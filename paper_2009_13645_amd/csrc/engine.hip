@@ -150,19 +150,23 @@ static Layout make_layout(const mithra_grid_desc *d, int64_t cap)
 // At most kKeep pieces of 2 MiB; all of it is released with the last handle
 // of the process.
 struct StagePool {
-    static constexpr size_t kKeep = 16;
+    static constexpr int kKeep = 16;
+    struct Piece {
+        int device;
+        char *p;
+    };
     std::mutex mu;
-    std::vector<std::pair<int, char *>> kept;  // device, memory
-    int handles = 0;
+    Piece kept[kKeep];
+    int n = 0, handles = 0;
 
     char *take(int device, size_t bytes)
     {
         {
             std::lock_guard<std::mutex> lk(mu);
-            for (size_t i = 0; i < kept.size(); ++i)
-                if (kept[i].first == device) {
-                    char *p = kept[i].second;
-                    kept.erase(kept.begin() + i);
+            for (int i = 0; i < n; ++i)
+                if (kept[i].device == device) {
+                    char *p = kept[i].p;
+                    kept[i] = kept[--n];
                     return p;
                 }
         }
@@ -178,8 +182,8 @@ struct StagePool {
     {
         {
             std::lock_guard<std::mutex> lk(mu);
-            if (idle && handles > 1 && kept.size() < kKeep) {
-                kept.emplace_back(device, p);
+            if (idle && handles > 1 && n < kKeep) {
+                kept[n++] = Piece{device, p};
                 return;
             }
         }
@@ -192,14 +196,16 @@ struct StagePool {
     }
     void handle_gone()
     {
-        std::vector<std::pair<int, char *>> drop;
+        Piece drop[kKeep];
+        int m = 0;
         {
             std::lock_guard<std::mutex> lk(mu);
             if (--handles == 0)
-                drop.swap(kept);
+                while (n > 0)
+                    drop[m++] = kept[--n];
         }
-        for (auto &k : drop)
-            (void)hipHostFree(k.second);
+        while (m > 0)
+            (void)hipHostFree(drop[--m].p);
     }
 };
 static StagePool g_stages;
