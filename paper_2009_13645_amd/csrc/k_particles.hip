@@ -25,15 +25,15 @@ constexpr int kLdsNodes = 1650;
 // EXT selects the general external field (undulator arrays, optical
 // undulators); the single static module keeps its own path.  SUBS: several
 // sub-steps.  In a loop over them the compiler keeps the field's polynomial
-// constants in registers across the whole push (161 VGPRs, 227 with the
-// general field), so runs of one sub-step, the usual case, have their own
-// body without it (124-154).
+// constants in registers across the whole push (143 VGPRs at FP32, 159 at FP64,
+// 205 with the general field), so runs of one sub-step, the usual case, have
+// their own body without it (122, 150 and 124 to 150).
 template <typename T, bool COMP, int MODE, bool EXT = false, bool SUBS = false>
 struct PushDeposit {
     // The block's box accumulates in FP64 LDS whatever the source precision
     // (an FP32 box measured 367 against 225 us per launch at the FEL
     // amplifier).  Three waves per SIMD: the box allows three blocks per CU.
-    // Sub-steps of the general external field need about 227 registers: two.
+    // Sub-steps of the general external field need 205 registers: two.
     using LT = double;
     static constexpr int kThreads = kDepThreads;
     static constexpr int kWaves = EXT && SUBS ? 2 : 3;
